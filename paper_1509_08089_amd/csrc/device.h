@@ -17,8 +17,7 @@ constexpr uint64_t kPhiloxW1 = 0xBB67AE8584CAA73Bull;
 // The 128-bit product a * b as four 32 x 32 -> 64-bit partial products, each one
 // multiply-add (v_mad_u64_u32); none of the partial sums exceeds 64 bits.  Spelled out
 // because the high half written as __umul64hi next to a 64-bit low product compiles to
-// about a third more multiplies (the Philox rounds are what the grouping pass spends
-// its time on).
+// about a third more multiplies.
 __device__ __forceinline__ void mul_wide(uint64_t a, uint64_t b, uint64_t& hi, uint64_t& lo) {
   const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32), b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
   const uint64_t p = (uint64_t)a0 * b0;
@@ -28,23 +27,80 @@ __device__ __forceinline__ void mul_wide(uint64_t a, uint64_t b, uint64_t& hi, u
   lo = (u << 32) | (uint32_t)p;
 }
 
-// Random words of block `blk` of sample `k`: counter (k, blk, 0, 0), key (seed, tag).
+// The two products of a Philox round, x0 * M0 and x2 * M1, each with its two middle partial
+// products added by one multiply-add whose carry out (bit 96 of the product) becomes the
+// upper word of the last addend: 4 multiply-adds and 3 other instructions a product
+// against mul_wide's 9 in all (a 64-bit addend needs its upper word cleared or copied by
+// moves).  The compiler has no form that yields the carry.  gfx950 wants two wait states
+// between a vector instruction that writes a scalar register and a vector instruction
+// that reads it, and the compiler does not look into the block for them: between each
+// multiply-add and the select of its carry there are two instructions, and the block reads
+// no scalar register from outside.
+__device__ __forceinline__ void philox_products(uint64_t x0, uint64_t x2, uint64_t& hi0, uint64_t& lo0,
+                                                uint64_t& hi1, uint64_t& lo1) {
+  constexpr uint32_t a0 = (uint32_t)kPhiloxM0, a1 = (uint32_t)(kPhiloxM0 >> 32);
+  constexpr uint32_t b0 = (uint32_t)kPhiloxM1, b1 = (uint32_t)(kPhiloxM1 >> 32);
+  const uint32_t xl = (uint32_t)x0, xh = (uint32_t)(x0 >> 32), yl = (uint32_t)x2, yh = (uint32_t)(x2 >> 32);
+  const uint64_t p = (uint64_t)xl * a0, q = (uint64_t)yl * b0;
+  uint64_t m = (uint64_t)xl * a1 + (p >> 32), n = (uint64_t)yl * b1 + (q >> 32);
+  uint32_t c, d;
+  uint64_t cc, dd;  // the carries, one bit per lane
+  asm("v_mad_u64_u32 %0, %4, %6, %8, %0\n\t"
+      "v_mad_u64_u32 %1, %5, %7, %9, %1\n\t"
+      "s_nop 0\n\t"
+      "v_cndmask_b32_e64 %2, 0, 1, %4\n\t"
+      "v_cndmask_b32_e64 %3, 0, 1, %5"
+      : "+&v"(m), "+&v"(n), "=&v"(c), "=&v"(d), "=&s"(cc), "=&s"(dd)
+      : "v"(xh), "v"(yh), "v"(a0), "v"(b0));
+  hi0 = (uint64_t)xh * a1 + (((uint64_t)c << 32) | (m >> 32));
+  lo0 = (m << 32) | (uint32_t)p;
+  hi1 = (uint64_t)yh * b1 + (((uint64_t)d << 32) | (n >> 32));
+  lo1 = (n << 32) | (uint32_t)q;
+}
+
+__device__ __forceinline__ uint64_t xor3(uint64_t a, uint64_t b, uint64_t c) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_bitop3_b32((int)(a >> 32), (int)(b >> 32), (int)(c >> 32), 0x96);
+  return (uint64_t)hi << 32 | lo;
+}
+
+// Random words of block `blk` of sample `k`: counter (k, blk, 0, 0), key (seed, tag);
+// blk, seed and tag are the same for every lane of the wave.
+//
+// Bound by VALU issue: every instruction of it takes an issue slot of about four cycles
+// whatever it is (a v_mad_u64_u32 as a v_xor_b32), so what counts is their number.  The
+// first round multiplies word 0 only (words 1 to 3 are blk, 0, 0) and the second's word 0
+// is uniform and multiplied on the scalar unit.  The round keys are made opaque per
+// block, so that the scalar unit computes them between the vector instructions (the
+// compiler otherwise keeps forty of them live across a sampling loop, in VGPR lanes, one
+// v_readlane_b32 each) and the three-way xors take one v_bitop3_b32 a word.  A round is
+// 18 vector instructions, a block 194 instead of 257; alone on the chip 1.99e11 -> 2.48e11
+// blocks/s, and a 256-request batch (two or three blocks a sample) 23.9 -> 22.1 ms.
 __device__ __forceinline__ void philox_block(uint64_t k, uint64_t blk, uint64_t seed, uint64_t tag,
                                              uint64_t out[4]) {
-  uint64_t x0 = k, x1 = blk, x2 = 0, x3 = 0;
   uint64_t k0 = seed, k1 = tag;
+  asm volatile("" : "+s"(k0), "+s"(k1));
+  uint64_t hi0, lo0, hi1, lo1;
+  // round 0
+  mul_wide(k, kPhiloxM0, hi0, lo0);
+  const uint64_t s0 = blk ^ k0;  // word 0 of every lane
+  uint64_t x2 = hi0 ^ k1;
+  const uint64_t y3 = lo0;
+  // round 1
+  k0 += kPhiloxW0;
+  k1 += kPhiloxW1;
+  mul_wide(s0, kPhiloxM0, hi0, lo0);
+  mul_wide(x2, kPhiloxM1, hi1, lo1);
+  uint64_t x0 = hi1 ^ k0, x1 = lo1, x3 = lo0;
+  x2 = y3 ^ (hi0 ^ k1);  // the bracket is uniform
 #pragma unroll
-  for (int round = 0; round < 10; ++round) {
-    if (round) {
-      k0 += kPhiloxW0;
-      k1 += kPhiloxW1;
-    }
-    uint64_t hi0, lo0, hi1, lo1;
-    mul_wide(x0, kPhiloxM0, hi0, lo0);
-    mul_wide(x2, kPhiloxM1, hi1, lo1);
-    x0 = hi1 ^ x1 ^ k0;
+  for (int round = 2; round < 10; ++round) {
+    k0 += kPhiloxW0;
+    k1 += kPhiloxW1;
+    philox_products(x0, x2, hi0, lo0, hi1, lo1);
+    x0 = xor3(hi1, x1, k0);
     x1 = lo1;
-    x2 = hi0 ^ x3 ^ k1;
+    x2 = xor3(hi0, x3, k1);
     x3 = lo0;
   }
   out[0] = x0;
