@@ -222,7 +222,7 @@ hipError_t launch_sample(int sampler, const SamplerView& v, uint64_t seed, uint6
                          unsigned long long* hits, uint8_t* class_out, int grid, int block, hipStream_t s);
 
 // The same samples drawn XCD-grouped, one chunk [a, a + n) at a time (n <= max_n <=
-// 2^31): the grouping passes (group of each sample, per-block group counts, their scan,
+// 2^26): the grouping passes (group of each sample, per-block group counts, their scan,
 // the sorted order) into `scratch`, which holds grouped_scratch_bytes(max_n) bytes, then
 // the sampling launch that reads them.  The two may run on different streams, ordered by
 // events; a scratch block serves one chunk at a time.  block must be 64, 128, 192 or 256

@@ -24,7 +24,6 @@
 // sample index), never on which lane, block or launch draws it.
 #include <algorithm>
 #include <mutex>
-#include <type_traits>
 
 #include "device.h"
 #include "kernels.h"
@@ -2430,8 +2429,17 @@ hipError_t launch_sample(int sampler, const SamplerView& v, uint64_t seed, uint6
 constexpr int kXcds = 8;
 constexpr int kSortBits = 10;
 constexpr int kSortGroups = 1 << kSortBits;
-using SortGroup = std::conditional_t<(kSortBits <= 8), uint8_t, uint16_t>;  // a sample's group
-static_assert(kSortGroups % 256 == 0 && kSortBits <= 16, "whole groups per scatter thread");
+static_assert(kSortGroups % 256 == 0 && kSortBits < 16, "whole groups per scatter thread");
+// The counting pass keeps the top 16 bits of a sample's first word: the group and, below
+// it, the lane bits, which order the samples of a window (lane order, above) and travel
+// in the top bits of the sorted order's entries, so that the sampling kernel sorts its
+// windows without drawing the words again (one Philox block of two or three a sample;
+// n = 1e5, m = 1e6, MOSS-4 for 1e7 samples: 473 -> 459 us an estimate; past the MALL, where
+// the fabric binds, no change).  6 bits order a 512-sample window into runs of 8, as far
+// as a wave of 64 lanes can tell.
+constexpr int kLaneBits = 16 - kSortBits;
+constexpr int kOrderBits = 32 - kLaneBits;  // a sample's offset in its chunk
+constexpr uint32_t kOrderMask = (1u << kOrderBits) - 1;
 constexpr uint32_t kSortSpan = 8192;   // samples per block of the counting passes
 static_assert(kSortSpan <= 65536 && kSortSpan % 16 == 0, "16-bit local offsets, 16-byte group loads");
 // Sorted entries a block takes per cursor step: 512 while the sampled tables fit the
@@ -2458,7 +2466,7 @@ constexpr int kMaxWindow = 512;         // sorted entries a block takes at a tim
 // column: the rows are cut into at most kSortRuns runs of consecutive blocks, each run
 // sums its rows per group, one wave per four groups scans those sums across the runs,
 // and each run then walks its rows again writing places.  All counts fit 32 bits (a
-// chunk has at most 2^31 samples).  Against a group-major table of 64-bit inclusive
+// chunk has at most 2^26 samples).  Against a group-major table of 64-bit inclusive
 // counts (one strided 8-byte store and load per (block, group), through the general
 // three-kernel scan): n = 1e5, m = 1e6, MOSS-4 for 1e7 samples, sampling launch 0.493
 // -> 0.476 ms; n = 1e6, m = 1e7, T-5 / Path-5 for 5e7 samples each, 5.58 / 7.57 ->
@@ -2468,8 +2476,8 @@ constexpr uint32_t kSortQuads = kSortGroups / 4;
 static_assert(kSortQuads == 256, "one group quad per thread of a 256-thread block");
 
 struct SortScratch {
-  SortGroup* group;   // n: group of each sample
-  uint32_t* order;    // n: sample offsets sorted by group
+  uint16_t* key;      // n: top 16 bits of each sample's first word (group, then lane bits)
+  uint32_t* order;    // n: sample offsets sorted by group, lane bits above them
   uint32_t* counts;   // nblk rows of kSortGroups: block b's count of group g at b * kSortGroups + g
   uint32_t* place;    // same layout: where run (b, g) starts in the sorted order
   uint32_t* rsum;     // kSortRuns rows of kSortGroups: per (run, group) sums, then their exclusive prefix
@@ -2507,7 +2515,7 @@ static SortScratch sort_scratch(void* base, uint64_t max_n) {
     return q;
   };
   set_runs(t, max_n);
-  t.group = reinterpret_cast<SortGroup*>(take(max_n * sizeof(SortGroup)));
+  t.key = reinterpret_cast<uint16_t*>(take(max_n * 2));
   t.order = reinterpret_cast<uint32_t*>(take(max_n * 4));
   t.counts = reinterpret_cast<uint32_t*>(take((size_t)kSortGroups * t.nblk * 4));
   t.place = reinterpret_cast<uint32_t*>(take((size_t)kSortGroups * t.nblk * 4));
@@ -2521,7 +2529,7 @@ static SortScratch sort_scratch(void* base, uint64_t max_n) {
 constexpr uint64_t scratch_bytes_for(uint64_t max_n) {
   const uint64_t nblk = std::max<uint64_t>(1, (max_n + kSortSpan - 1) / kSortSpan);
   auto r = [](uint64_t b) { return (b + 255) / 256 * 256; };
-  return r(max_n * sizeof(SortGroup)) + r(max_n * 4) + 2 * r(kSortGroups * nblk * 4) +
+  return r(max_n * 2) + r(max_n * 4) + 2 * r(kSortGroups * nblk * 4) +
          r(kSortGroups * kSortRuns * 4) + r(kSortGroups * 4) + r((kSortGroups + 1) * 4) +
          r(kXcds * kCursorStride * 4) + 256;
 }
@@ -2579,9 +2587,9 @@ __global__ __launch_bounds__(256) void k_sort_count(uint64_t seed, uint64_t k0, 
   for (uint64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
     uint64_t W[4];
     philox_block(k0 + i, 0, seed, S, W);
-    const uint32_t g = (uint32_t)(W[0] >> (64 - kSortBits));
-    t.group[i] = (SortGroup)g;
-    atomicAdd(&hist[g], 1u);
+    const uint32_t key = (uint32_t)(W[0] >> 48);
+    t.key[i] = (uint16_t)key;
+    atomicAdd(&hist[key >> kLaneBits], 1u);
   }
   __syncthreads();
   for (int g = threadIdx.x; g < kSortGroups; g += blockDim.x) t.counts[(size_t)blockIdx.x * kSortGroups + g] = hist[g];
@@ -2672,7 +2680,7 @@ __global__ __launch_bounds__(256) void k_sort_scatter(uint64_t n, SortScratch t)
   __shared__ uint32_t next[kSortGroups];   // per group: the run's fill cursor
   __shared__ uint32_t wsum[4];
   __shared__ uint16_t local[kSortSpan];    // span offsets sorted by group
-  __shared__ __align__(16) SortGroup grp[kSortSpan];
+  __shared__ __align__(16) uint16_t key[kSortSpan];
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;  // blockDim.x == 256
   const uint64_t lo = (uint64_t)blockIdx.x * kSortSpan;
   const uint32_t len = (uint32_t)(n < lo + kSortSpan ? n - lo : kSortSpan);
@@ -2688,10 +2696,10 @@ __global__ __launch_bounds__(256) void k_sort_scatter(uint64_t n, SortScratch t)
     mine += size[j];
   }
   if (len == kSortSpan) {  // whole span: 16-byte loads
-    for (uint32_t j = tid; j < kSortSpan * sizeof(SortGroup) / 16; j += blockDim.x)
-      reinterpret_cast<uint4*>(grp)[j] = reinterpret_cast<const uint4*>(t.group + lo)[j];
+    for (uint32_t j = tid; j < kSortSpan * 2 / 16; j += blockDim.x)
+      reinterpret_cast<uint4*>(key)[j] = reinterpret_cast<const uint4*>(t.key + lo)[j];
   } else {
-    for (uint32_t j = tid; j < len; j += blockDim.x) grp[j] = t.group[lo + j];
+    for (uint32_t j = tid; j < len; j += blockDim.x) key[j] = t.key[lo + j];
   }
   // exclusive prefix of the share sizes in group order: local run starts
   bool unused = false;
@@ -2708,12 +2716,12 @@ __global__ __launch_bounds__(256) void k_sort_scatter(uint64_t n, SortScratch t)
     off += size[j];
   }
   __syncthreads();
-  for (uint32_t j = tid; j < len; j += blockDim.x) local[atomicAdd(&next[grp[j]], 1u)] = (uint16_t)j;
+  for (uint32_t j = tid; j < len; j += blockDim.x) local[atomicAdd(&next[key[j] >> kLaneBits], 1u)] = (uint16_t)j;
   __syncthreads();
   for (uint32_t j = tid; j < len; j += blockDim.x) {
     const uint32_t o = local[j];
-    const uint32_t g = grp[o];
-    t.order[(uint64_t)base[g] + (j - start[g])] = (uint32_t)(lo + o);
+    const uint32_t k = key[o], g = k >> kLaneBits;
+    t.order[(uint64_t)base[g] + (j - start[g])] = (uint32_t)(lo + o) | (k << kOrderBits);
   }
 }
 
@@ -2725,11 +2733,12 @@ __global__ __launch_bounds__(256, 8) void k_sample_sorted(SamplerView a, uint64_
   __shared__ uint32_t bins[kMaxWaves][kBins + 2];
   __shared__ uint8_t lut[64];
   __shared__ uint32_t s_win;
-  __shared__ LaneSort<kMaxWindow> ls;
+  __shared__ uint32_t next[1 << kLaneBits];  // lane-bit counts, then each bucket's next place
+  __shared__ uint32_t entry[kMaxWindow];     // the window's entries in lane order
   const int tid = threadIdx.x, wave = tid >> 6, nw = blockDim.x >> 6;
   for (int i = tid; i < nw * (kBins + 2); i += blockDim.x) bins[i / (kBins + 2)][i % (kBins + 2)] = 0;
   load_lut<S>(lut);
-  __syncthreads();
+  static_assert(kLaneBits == 6, "one bucket per lane of the scanning wave");
   // start of group g in the sorted order
   auto start = [&](uint32_t g) -> uint64_t { return g >= (uint32_t)kSortGroups ? n : (uint64_t)t.gstart[g]; };
   const uint32_t per_xcd = kSortGroups / kXcds;
@@ -2737,22 +2746,42 @@ __global__ __launch_bounds__(256, 8) void k_sample_sorted(SamplerView a, uint64_
     const uint32_t x = (uint32_t)((blockIdx.x + step) % kXcds);
     const uint64_t lo = start(x * per_xcd), hi = start((x + 1) * per_xcd);
     for (;;) {
+      if (tid < (1 << kLaneBits)) next[tid] = 0;
       if (tid == 0) s_win = atomicAdd(&t.cursors[x * kCursorStride], 1u);
       __syncthreads();
       const uint64_t p = lo + (uint64_t)s_win * window;
-      __syncthreads();
-      if (p >= hi) break;
+      if (p >= hi) {
+        __syncthreads();  // s_win is written again below
+        break;
+      }
       const uint32_t m = (uint32_t)((hi < p + window ? hi : p + window) - p);
-      // lane order inside the window: its samples share the group (the top kSortBits
-      // bits of the first word); the next 8 bits order them
-      lane_sort<S>(ls, seed, [&](uint32_t j) { return k0 + t.order[p + j]; }, m, 64 - kSortBits - 8);
+      // lane order inside the window: its samples share the group, the lane bits order them
+      const uint32_t* __restrict__ win = t.order + p;
+      for (uint32_t j = tid; j < m; j += blockDim.x) atomicAdd(&next[win[j] >> kOrderBits], 1u);
+      __syncthreads();
+      if (wave == 0) {  // exclusive prefix of the counts, one per lane
+        const uint32_t c = next[tid];
+        uint32_t incl = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const uint32_t y = __shfl_up(incl, off, 64);
+          if (tid >= off) incl += y;
+        }
+        next[tid] = incl - c;
+      }
+      __syncthreads();
       for (uint32_t j = tid; j < m; j += blockDim.x) {
-        const uint64_t i = t.order[p + ls.order[j]];
+        const uint32_t e = win[j];
+        entry[atomicAdd(&next[e >> kOrderBits], 1u)] = e;
+      }
+      __syncthreads();
+      for (uint32_t j = tid; j < m; j += blockDim.x) {
+        const uint32_t i = entry[j] & kOrderMask;
         const int c = draw<S>(a, lut, seed, k0 + i, nullptr);
         count_sample(bins[wave], c);
         if (class_out) class_out[i] = (uint8_t)c;
       }
-      __syncthreads();  // the next window reuses ls
+      __syncthreads();  // the next window reuses the counts, the entries and s_win
     }
   }
   __syncthreads();
@@ -2765,7 +2794,7 @@ __global__ __launch_bounds__(256, 8) void k_sample_sorted(SamplerView a, uint64_
 
 hipError_t launch_group_chunk(int sampler, uint64_t seed, uint64_t a, uint64_t n, void* scratch, uint64_t max_n,
                               hipStream_t s) {
-  if (n == 0 || n > max_n || max_n > (1ull << 31)) return hipErrorInvalidValue;
+  if (n == 0 || n > max_n || max_n > (1ull << kOrderBits)) return hipErrorInvalidValue;
   SortScratch tc = sort_scratch(scratch, max_n);
   set_runs(tc, n);
   const uint32_t nblk = tc.nblk;
@@ -2786,8 +2815,8 @@ hipError_t launch_group_chunk(int sampler, uint64_t seed, uint64_t a, uint64_t n
 hipError_t launch_sample_chunk(int sampler, const SamplerView& v, uint64_t seed, uint64_t a, uint64_t n,
                                void* scratch, uint64_t max_n, uint32_t window, unsigned long long* hits,
                                uint8_t* class_out, int grid, int block, hipStream_t s) {
-  if (block != 64 * (block / 64) || block > 256 || block < 64 || n == 0 || n > max_n || max_n > (1ull << 31) ||
-      window == 0 || window > (uint32_t)kMaxWindow)
+  if (block != 64 * (block / 64) || block > 256 || block < 64 || n == 0 || n > max_n ||
+      max_n > (1ull << kOrderBits) || window == 0 || window > (uint32_t)kMaxWindow)
     return hipErrorInvalidValue;
   SortScratch tc = sort_scratch(scratch, max_n);
   set_runs(tc, n);
