@@ -144,6 +144,11 @@ __device__ __forceinline__ int row_guide_shift(uint64_t total, int g) {
   return bl > g ? bl - g : 0;
 }
 
+__device__ __forceinline__ int row_guide_shift(uint32_t total, int g) {
+  const int bl = total ? 32 - __clz((int)total) : 0;
+  return bl > g ? bl - g : 0;
+}
+
 // ---------------------------------------------------------------------------------
 // CSR validation and layout at creation.  k_node_prep checks row_ptr; the kernels
 // after it read the error word first and do nothing once row_ptr is rejected, so
@@ -400,8 +405,10 @@ __global__ __launch_bounds__(256) void k_filter_build(const uint64_t* __restrict
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (key[j] == kEmptySlot) continue;
-        const uint64_t m = filter_mask(mix64(key[j]));
-        const uint64_t w = edge_slot(key[j], filter_bits);
+        const EdgeHash h = edge_hash(key[j]);
+        const uint2 bits = filter_mask(h);
+        const uint64_t m = (uint64_t)bits.y << 32 | bits.x;
+        const uint64_t w = edge_slot(h, filter_bits);
         if (w == (s0 >> shift)) mine |= m;
         else atomicOr(&filter[w], (unsigned long long)m);
       }
@@ -2018,29 +2025,22 @@ hipError_t launch_guides(const GuideSet& set, int32_t n, int gbits, hipStream_t 
   return hipGetLastError();
 }
 
-// Weighted pick in a row: the first entry i of the row whose inclusive prefix
-// value(i) exceeds x (x < total = value(d-1)).
-template <typename F>
-__device__ __forceinline__ int32_t row_pick(F value, int32_t d, uint64_t total, uint64_t x,
+// Weighted pick in a row: the first entry i of the row whose inclusive prefix acc[i]
+// exceeds x (x < total = acc[d-1]).
+template <typename T>
+__device__ __forceinline__ int32_t row_pick(const T* __restrict__ acc, int32_t d, T total, T x,
                                             const uint32_t* __restrict__ guide, uint32_t goff) {
-  if (d < kRowGuideMin) return first_above_by(value, 0, d - 1, x);
-  const int g = row_guide_bits(d);
-  const uint64_t b = x >> row_guide_shift(total, g);
-  const uint2 w = load_pair(guide + goff + b);  // guide[b], guide[b + 1]
-  // the window lies inside the row for any guide contents (a correct guide needs no clamp)
-  const int32_t hi = min((int32_t)w.y, d - 1);
-  return first_above_by(value, min((int32_t)w.x, hi), hi, x);
+  int32_t lo = 0, hi = d - 1;
+  if (d >= kRowGuideMin) {
+    const int g = row_guide_bits(d);
+    const uint32_t b = (uint32_t)(x >> row_guide_shift(total, g));
+    const uint2 w = load_pair(guide + goff + b);  // guide[b], guide[b + 1]
+    // the window lies inside the row for any guide contents (a correct guide needs no clamp)
+    hi = min((int32_t)w.y, hi);
+    lo = min((int32_t)w.x, hi);
+  }
+  return first_above_wide(acc, d, lo, hi, x);
 }
-
-struct PrefixOf32 {
-  const uint32_t* __restrict__ acc;
-  __device__ uint64_t operator()(int32_t i) const { return (uint64_t)acc[i]; }
-};
-
-struct PrefixOf64 {
-  const uint64_t* __restrict__ acc;
-  __device__ uint64_t operator()(int32_t i) const { return acc[i]; }
-};
 
 // ---------------------------------------------------------------------------------
 // The samplers.  Each returns the motif class of sample k (0 = rejected) and, when
@@ -2050,14 +2050,14 @@ __device__ __forceinline__ int32_t pick_node(const SamplerView& a, uint64_t x) {
   const uint64_t r = bounded(x, a.total);
   const uint32_t b = (uint32_t)(x >> (64 - a.gbits));
   const uint2 w = load_pair(a.guide + b);  // guide[b], guide[b + 1]
-  return first_above(a.acc_node, (int32_t)w.x, (int32_t)w.y, r);
+  return first_above_wide(a.acc_node, a.n, (int32_t)w.x, (int32_t)w.y, r);
 }
 
 // RandomVertex(N_a - {skip}) with skip in N_a: index j uniform over the row with
 // skip's slot removed; the sorted row is read at j and stepped past skip.
 __device__ __forceinline__ int32_t neighbour_except(const int32_t* __restrict__ col, int32_t ra, int32_t da,
                                                     int32_t skip, uint64_t word) {
-  const int32_t j = (int32_t)bounded(word, (uint64_t)(da - 1));
+  const int32_t j = (int32_t)bounded32(word, (uint32_t)(da - 1));
   const uint2 x = load_pair(col + ra + j);  // j + 1 <= da - 1: both inside the row
   return (int32_t)x.x >= skip ? (int32_t)x.y : (int32_t)x.x;
 }
@@ -2075,9 +2075,10 @@ __device__ __forceinline__ int probe_edges(const SamplerView& a, const int32_t (
   for (int i = 0; i < P; ++i) {
     asm volatile("" ::: "memory");
     const uint64_t key = edge_key(x[i], y[i]);
-    const uint64_t fm = filter_mask(mix64(key));
-    if ((a.filter[edge_slot(key, a.filter_bits)] & fm) != fm) continue;
-    const uint64_t h = edge_slot(key, a.edge_bits);
+    const EdgeHash eh = edge_hash(key);
+    const uint2 word = reinterpret_cast<const uint2*>(a.filter)[edge_slot(eh, a.filter_bits)];
+    if (!filter_has(word, filter_mask(eh))) continue;
+    const uint64_t h = edge_slot(eh, a.edge_bits);
     if (edge_hash_rest(a.edge_slots, a.edge_bits, key, h, a.edge_slots[h])) m |= 1 << i;
   }
   return m;
@@ -2094,9 +2095,9 @@ __device__ __forceinline__ int draw_moss4(const SamplerView& a, const uint8_t* l
   const int32_t v = pick_node(a, W[0]);
   const uint4 R = a.rec[v];
   const int32_t rv = (int32_t)R.x, dv = (int32_t)R.y;
-  const int32_t iu = row_pick(PrefixOf32{a.acc_sigma + rv}, dv, R.z, bounded(W[1], R.z), a.sig_guide, R.w);
+  const int32_t iu = row_pick(a.acc_sigma + rv, dv, R.z, bounded32(W[1], R.z), a.sig_guide, R.w);
   const int32_t u = col[rv + iu];
-  int32_t iw = (int32_t)bounded(W[2], (uint64_t)(dv - 1));
+  int32_t iw = (int32_t)bounded32(W[2], (uint32_t)(dv - 1));
   iw += iw >= iu;
   const int32_t w = col[rv + iw];
   const uint2 U = row_of(a.rec, u);
@@ -2147,12 +2148,12 @@ __device__ __forceinline__ int draw_moss4min(const SamplerView& a, const uint8_t
   const int32_t rv = (int32_t)R.x, dv = (int32_t)R.y;
   const uint64_t* __restrict__ chk = a.acc_check + rv;
   const uint64_t T = chk[dv - 1];
-  const int32_t iu = row_pick(PrefixOf64{chk}, dv, T, bounded(W[1], T), a.check_guide, R.w);
+  const int32_t iu = row_pick(chk, dv, T, bounded(W[1], T), a.check_guide, R.w);
   const int32_t u = a.col[rv + iu];
   const uint2 rk = a.rank[rv + iu];  // d_{v,u}, d_{u,v}: both >= 1 for a drawn entry
-  const int32_t w = a.col_rank[rv + (int32_t)bounded(W[2], (uint64_t)rk.x)];
+  const int32_t w = a.col_rank[rv + (int32_t)bounded32(W[2], rk.x)];
   const uint2 U = row_of(a.rec, u);
-  const int32_t r = a.col_rank[(int32_t)U.x + (int32_t)bounded(W[3], (uint64_t)rk.y)];
+  const int32_t r = a.col_rank[(int32_t)U.x + (int32_t)bounded32(W[3], rk.y)];
   if (nodes) {
     nodes[0] = v; nodes[1] = u; nodes[2] = w; nodes[3] = r; nodes[4] = -1;
   }
@@ -2185,13 +2186,13 @@ __device__ __forceinline__ int draw_t5(const SamplerView& a, const uint8_t* lut,
   const int32_t v = pick_node(a, W[0]);
   const uint4 R = a.rec[v];
   const int32_t rv = (int32_t)R.x, dv = (int32_t)R.y;
-  const int32_t iu = row_pick(PrefixOf32{a.acc_sigma + rv}, dv, R.z, bounded(W[1], R.z), a.sig_guide, R.w);
+  const int32_t iu = row_pick(a.acc_sigma + rv, dv, R.z, bounded32(W[1], R.z), a.sig_guide, R.w);
   const int32_t u = col[rv + iu];
-  int32_t iw = (int32_t)bounded(W[2], (uint64_t)(dv - 1));
+  int32_t iw = (int32_t)bounded32(W[2], (uint32_t)(dv - 1));
   iw += iw >= iu;
   const int32_t w = col[rv + iw];
   const int32_t lo = min(iu, iw), hi = max(iu, iw);
-  int32_t ir = (int32_t)bounded(W[3], (uint64_t)(dv - 2));
+  int32_t ir = (int32_t)bounded32(W[3], (uint32_t)(dv - 2));
   ir += ir >= lo;
   ir += ir >= hi;
   const int32_t r = col[rv + ir];
@@ -2222,11 +2223,11 @@ __device__ __forceinline__ int draw_path5(const SamplerView& a, const uint8_t* l
   const int32_t rv = (int32_t)R.x, dv = (int32_t)R.y;
   const uint64_t* __restrict__ tau = a.acc_tau + rv;
   const uint64_t T = tau[dv - 1];
-  const int32_t iu = row_pick(PrefixOf64{tau}, dv, T, bounded(W[1], T), a.tau_guide, R.w);
+  const int32_t iu = row_pick(tau, dv, T, bounded(W[1], T), a.tau_guide, R.w);
   const int32_t u = col[rv + iu];
   const uint32_t* __restrict__ sig = a.acc_sigma + rv;
-  const uint64_t Sv = R.z;
-  uint64_t blk_lo, blk_hi;  // u's block of ACC_sigma: [sig[iu - 1], sig[iu])
+  const uint32_t Sv = R.z;
+  uint32_t blk_lo, blk_hi;  // u's block of ACC_sigma: [sig[iu - 1], sig[iu])
   if (iu > 0) {
     const uint2 s2 = load_pair(sig + iu - 1);
     blk_lo = s2.x;
@@ -2235,10 +2236,10 @@ __device__ __forceinline__ int draw_path5(const SamplerView& a, const uint8_t* l
     blk_lo = 0;
     blk_hi = sig[0];
   }
-  const uint64_t du1 = blk_hi - blk_lo;
-  uint64_t x = bounded(W[2], Sv - du1);
+  const uint32_t du1 = blk_hi - blk_lo;
+  uint32_t x = bounded32(W[2], Sv - du1);
   x += x >= blk_lo ? du1 : 0;
-  const int32_t iw = row_pick(PrefixOf32{sig}, dv, Sv, x, a.sig_guide, R.w);
+  const int32_t iw = row_pick(sig, dv, Sv, x, a.sig_guide, R.w);
   const int32_t w = col[rv + iw];
   const uint2 U = row_of(a.rec, u), Wr = row_of(a.rec, w);
   const int32_t ru = (int32_t)U.x, du = (int32_t)U.y, rw = (int32_t)Wr.x, dw = (int32_t)Wr.y;
