@@ -217,6 +217,7 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
 // ---- edge hash set: open addressing with linear probing over 2^bits u64 slots ----
 constexpr uint64_t kEmptySlot = ~0ull;
+constexpr uint64_t kNoSlot = ~0ull - 1;  // no key and not empty: node ids stay below 2^31
 
 __device__ __forceinline__ uint64_t edge_key(int32_t a, int32_t b) {
   const uint32_t lo = (uint32_t)min(a, b), hi = (uint32_t)max(a, b);
