@@ -91,6 +91,7 @@ SamplerView sampler_view(const moss_graph* g, int sampler) {
   v.edge_bits = g->edge_bits;
   v.filter = g->filter;
   v.filter_bits = g->filter_bits;
+  v.hub_filter = has_hub_filters(g) ? g->hub_filter : nullptr;
   v.rank = g->rank;
   v.col_rank = g->col_rank;
   v.acc_check = g->acc_check;
@@ -296,7 +297,7 @@ T* at(void* base, size_t off) {
 // scan scratch, partials, records
 struct GraphLayout {
   size_t small, slots, filter, items, item_sum, guide_len, tmp[3], partials, rec, span_row, check_part, span_sums,
-      span_groups, group_wrap, bytes;
+      span_groups, group_wrap, hub_filter, bytes;
 };
 
 GraphLayout graph_layout(int32_t n, int64_t nnz) {
@@ -317,6 +318,7 @@ GraphLayout graph_layout(int32_t n, int64_t nnz) {
   L.span_sums = c.take<uint64_t>(2 * (size_t)std::max<int64_t>(1, span_count(nnz)));
   L.span_groups = c.take<uint64_t>((size_t)std::max<int64_t>(1, span_group_count(nnz)));
   L.group_wrap = c.take<uint32_t>((size_t)std::max<int64_t>(1, span_group_count(nnz)));
+  L.hub_filter = c.take<uint8_t>((size_t)nnz);
   L.bytes = c.off;
   return L;
 }
@@ -508,6 +510,7 @@ moss_status finish_create(moss_graph* g) {
   g->span_sums = at<uint64_t>(m, L.span_sums);
   g->span_groups = at<uint64_t>(m, L.span_groups);
   g->group_wrap = at<uint32_t>(m, L.group_wrap);
+  g->hub_filter = at<uint64_t>(m, L.hub_filter);
   if (!(g->h_stage = pinned_chunk())) return MOSS_E_NOMEM;
   if (!(g->ev0 = pooled_event(g->device)) || !(g->ev1 = pooled_event(g->device))) return MOSS_E_DEVICE;
   hipStream_t s = g->stream;
@@ -840,6 +843,8 @@ moss_status moss::build_tables(moss_graph* g, uint32_t k_mask) {
   t.rec = g->rec;
   t.nnz = g->nnz;
   t.n = g->n;
+  if (e == hipSuccess && want_sig && has_hub_filters(g))
+    e = launch_hub_filter(g->nnz, g->span_row, g->rec, g->col, g->hub_filter, s);
   if (e == hipSuccess && want_sig) {
     t.guide = g->sig_guide;
     e = launch_row_tables(kRowSigma, t, err, s);

@@ -278,6 +278,15 @@ __device__ __forceinline__ bool filter_has(uint2 word, uint2 mask) {
   return ((~word.x & mask.x) | (~word.y & mask.y)) == 0;
 }
 
+// Where a row's hub filter lies (in 8-byte words), and the word of a key in it.
+__device__ __forceinline__ uint32_t hub_first(uint32_t start) { return (start + 63) / 64 * 8; }
+__device__ __forceinline__ uint32_t hub_words(uint32_t start, uint32_t d) {
+  return (start + d) / 64 * 8 - hub_first(start);
+}
+__device__ __forceinline__ uint32_t hub_word(uint32_t start, uint32_t d, EdgeHash h) {
+  return hub_first(start) + __umulhi(h.top, hub_words(start, d));
+}
+
 // Inclusive scan over the 64 lanes of a wave; `wrapped` is set on any 64-bit wrap.
 __device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t x, bool& wrapped) {
   const int lane = lane_id();

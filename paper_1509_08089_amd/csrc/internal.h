@@ -43,6 +43,7 @@ struct moss_graph {
   uint64_t* span_sums = nullptr;         // 2 per span: the row-prefix passes' span sums
   uint64_t* span_groups = nullptr;       // per 64 spans: their summed span sums
   uint32_t* group_wrap = nullptr;        // per 64 spans: whether that sum wrapped
+  uint64_t* hub_filter = nullptr;        // nnz bytes: hub rows' own filters
   int64_t n_items = 0;
   int64_t row_guide_len = 0;             // entries of one row-guide array
 
@@ -76,6 +77,11 @@ struct moss_graph {
 };
 
 namespace moss {
+
+// whether g's hub rows have filters of their own
+inline bool has_hub_filters(const moss_graph* g) {
+  return !(g->flags & MOSS_TRUST_CSR) && g->max_degree >= kHubMinDegree && g->filter_bits >= kHubMinFilterBits;
+}
 
 // index of a sampler's node distribution / tables
 inline int sampler_slot(int sampler) {

@@ -37,6 +37,7 @@ struct SamplerView {
   const uint32_t* tau_guide;  // row guides over ACC_tau (Path-5)
   const uint64_t* edge_slots; // edge hash set: 2^edge_bits slots, key min << 32 | max
   const uint64_t* filter;     // edge filter: 2^filter_bits words of 64 bits
+  const uint64_t* hub_filter; // hub rows' own filters (null: none)
   const uint2* rank;          // MOSS-4Min, per entry (v, x): {d_{v,x}, d_{x,v}}
   const int32_t* col_rank;    // MOSS-4Min: each row in descending order (N_{v,x} = its first d_{v,x})
   const uint64_t* acc_check;  // MOSS-4Min: row-local inclusive prefix of d_{v,x} d_{x,v}
@@ -198,6 +199,20 @@ hipError_t launch_row_totals(int32_t n, const int32_t* rp, const uint64_t* acc, 
 // filter size (2^bits 64-bit words, bits >= 1).
 int edge_hash_bits(int64_t m);
 int edge_filter_bits(int64_t m);
+
+// Hub filters (k_hub_filter): rows of at least kHubMinDegree entries have a filter of their
+// own, on graphs whose edge filter is at least 2^kHubMinFilterBits words (1 MB, more than
+// 2^19 edges; below, the edge filter itself stays cached).  Measured with rows of at least
+// 4096 / 2048 / 1024 / 512 / 256 / 128 entries (none: 12.68 ms, 442 us): 1e8 samples at
+// n = 1e6, m = 1e7, k = 5, 12.19 / 11.99 / 11.78 / 11.62 / 11.51 / 11.45 ms; 1e7 samples at
+// n = 1e5, m = 1e6, k = 4, 435 / 436 / 431 / 429 / 429 / 430 us.  Building them takes 65 us
+// of the 2.9 ms of all tables at m = 1e7.  A row lists its edges only in a checked CSR (in an
+// unchecked one the edge set takes every edge from its smaller end), so unchecked graphs do
+// without.
+constexpr int32_t kHubMinDegree = 256;
+constexpr int kHubMinFilterBits = 17;
+hipError_t launch_hub_filter(int64_t nnz, const int32_t* span_row, const uint4* rec, const int32_t* col, uint64_t* hub,
+                             hipStream_t s);
 
 // Node weights (any output may be null) from the node records' S_v and the ACC_tau row
 // ends, and Lambda_3, Lambda_4 into lambdas[0..1]; partials must hold

@@ -420,6 +420,68 @@ __global__ __launch_bounds__(256) void k_filter_build(const uint64_t* __restrict
   }
 }
 
+// Hub filters: a filter of its own for every row of at least kHubMinDegree entries, a byte
+// an entry, in the 64-byte units that lie inside the row's own stretch of an array of nnz
+// bytes, so that a row's start and degree say where it is.  A probe of v's or u's row reads
+// it there: the windows and chunks in lane order share v, so those reads stay in the L1
+// and L2 and only the pairs without a hub go to the large filter.
+// A hub holds the first entry of some span (kHubMinDegree >= kSpan), and the first such
+// span finds it.  A block puts a hub's filter together in LDS, kSeg words at a time.
+__global__ __launch_bounds__(256) void k_hub_filter(int64_t nnz, const int32_t* __restrict__ span_row,
+                                                    const uint4* __restrict__ rec, const int32_t* __restrict__ col,
+                                                    uint2* __restrict__ hub) {
+  constexpr uint32_t kSeg = 2048;
+  __shared__ uint32_t bits[2 * kSeg];
+  __shared__ int32_t list[64];
+  __shared__ uint32_t found;
+  const int tid = threadIdx.x;
+  const int64_t spans = (nnz + kSpan - 1) / kSpan;
+  for (int64_t s0 = (int64_t)blockIdx.x * 64; s0 < spans; s0 += (int64_t)gridDim.x * 64) {
+    if (tid < 64) {
+      const int64_t sp = s0 + tid;
+      const int32_t v = sp < spans ? span_row[sp] : 0;
+      const bool first = sp < spans && (sp == 0 || span_row[sp - 1] != v);
+      const bool is = first && row_of(rec, v).y >= (uint32_t)kHubMinDegree;
+      const uint64_t all = __ballot(is);
+      if (is) list[__popcll(all & ((1ull << tid) - 1))] = v;
+      if (tid == 0) found = (uint32_t)__popcll(all);
+    }
+    __syncthreads();
+    const uint32_t hubs = found;
+    for (uint32_t i = 0; i < hubs; ++i) {
+      const int32_t v = list[i];
+      const uint2 R = row_of(rec, v);
+      const uint32_t first = hub_first(R.x), words = hub_words(R.x, R.y);
+      for (uint32_t w0 = 0; w0 < words; w0 += kSeg) {
+        const uint32_t len = min(kSeg, words - w0);
+        for (uint32_t j = tid; j < 2 * len; j += 256) bits[j] = 0;
+        __syncthreads();
+        for (uint32_t j = tid; j < R.y; j += 256) {
+          const EdgeHash h = edge_hash(edge_key(v, col[(int64_t)R.x + j]));
+          const uint32_t w = hub_word(R.x, R.y, h) - first - w0;
+          if (w >= len) continue;
+          const uint2 m = filter_mask(h);
+          atomicOr(&bits[2 * w], m.x);
+          atomicOr(&bits[2 * w + 1], m.y);
+        }
+        __syncthreads();
+        for (uint32_t j = tid; j < len; j += 256) hub[(size_t)first + w0 + j] = make_uint2(bits[2 * j], bits[2 * j + 1]);
+        __syncthreads();
+      }
+    }
+    __syncthreads();  // the list is written again
+  }
+}
+
+hipError_t launch_hub_filter(int64_t nnz, const int32_t* span_row, const uint4* rec, const int32_t* col, uint64_t* hub,
+                             hipStream_t s) {
+  if (nnz <= 0) return hipSuccess;
+  static_assert(kHubMinDegree >= kSpan, "every hub holds a span's first entry");
+  hipLaunchKernelGGL(k_hub_filter, dim3((unsigned)std::min<int64_t>((span_count(nnz) + 63) / 64, 65536)), dim3(256), 0,
+                     s, nnz, span_row, rec, col, reinterpret_cast<uint2*>(hub));
+  return hipGetLastError();
+}
+
 hipError_t launch_edge_insert(int64_t nnz, const int32_t* span_row, const int32_t* rp, const int32_t* col, int32_t n,
                               uint64_t* slots, int hash_bits, uint64_t* filter, int filter_bits, uint64_t* small,
                               hipStream_t s) {
@@ -2062,6 +2124,9 @@ __device__ __forceinline__ int32_t neighbour_except(const int32_t* __restrict__ 
   return (int32_t)x.x >= skip ? (int32_t)x.y : (int32_t)x.x;
 }
 
+// A pair neither of whose nodes has its row at hand.
+#define kNoRow make_uint2(0u, 0u)
+
 // Induced-edge probes of one sample (the CIS() step of Algorithms 1, 3 and 4): bit i
 // of the result is set when {x[i], y[i]} is an edge.  A pair the filter turns away is
 // no edge; the others are looked up in the hash set.  The pairs go three at a time: their
@@ -2073,7 +2138,8 @@ __device__ __forceinline__ int32_t neighbour_except(const int32_t* __restrict__ 
 // 476 -> 465 us; past the MALL, where the fabric binds, 1% slower (12.53 -> 12.71 ms for
 // 1e8 samples at m = 1e7), which the hub filters win back (below).
 template <int P>
-__device__ __forceinline__ int probe_edges(const SamplerView& a, const int32_t (&x)[P], const int32_t (&y)[P]) {
+__device__ __forceinline__ int probe_edges(const SamplerView& a, const int32_t (&x)[P], const int32_t (&y)[P],
+                                           const uint2 (&row)[P]) {
   static_assert(P % 3 == 0, "three pairs at a time");
   const uint32_t last_slot = 0xFFFFFFFFu >> (32 - a.edge_bits);
   int m = 0;
@@ -2086,7 +2152,10 @@ __device__ __forceinline__ int probe_edges(const SamplerView& a, const int32_t (
     for (int i = 0; i < 3; ++i) {
       key[i] = edge_key(x[i0 + i], y[i0 + i]);
       eh[i] = edge_hash(key[i]);
-      word[i] = reinterpret_cast<const uint2*>(a.filter)[edge_slot(eh[i], a.filter_bits)];
+      const uint2* at = reinterpret_cast<const uint2*>(a.filter) + edge_slot(eh[i], a.filter_bits);
+      if (a.hub_filter && row[i0 + i].y >= (uint32_t)kHubMinDegree)
+        at = reinterpret_cast<const uint2*>(a.hub_filter) + hub_word(row[i0 + i].x, row[i0 + i].y, eh[i]);
+      word[i] = *at;
     }
     uint32_t pass = 0;
 #pragma unroll
@@ -2138,7 +2207,8 @@ __device__ __forceinline__ int draw_moss4(const SamplerView& a, const uint8_t* l
   }
   if (r == w) return 0;
   const int32_t px[3] = {u, v, w}, py[3] = {w, r, r};
-  return lut[probe_edges<3>(a, px, py)];
+  const uint2 row[3] = {U, make_uint2(R.x, R.y), kNoRow};
+  return lut[probe_edges<3>(a, px, py, row)];
 }
 
 // Reach count of a MOSS-4Min sample (Section 4.2.1): the ordered draws (w, v, u, r) of
@@ -2189,7 +2259,8 @@ __device__ __forceinline__ int draw_moss4min(const SamplerView& a, const uint8_t
   }
   if (r == w) return 0;
   const int32_t px[3] = {u, v, w}, py[3] = {w, r, r};
-  const int m = probe_edges<3>(a, px, py);
+  const uint2 row[3] = {U, make_uint2(R.x, R.y), kNoRow};
+  const int m = probe_edges<3>(a, px, py, row);
   const int c = lut[m];
   if (c != 5) return c;
   // known v-u (0,1), v-w (0,2), u-r (1,3); probed u-w (1,2), v-r (0,3), w-r (2,3)
@@ -2234,7 +2305,8 @@ __device__ __forceinline__ int draw_t5(const SamplerView& a, const uint8_t* lut,
   }
   if (t == w || t == r) return 0;
   const int32_t px[6] = {u, u, w, v, w, r}, py[6] = {w, r, r, t, t, t};
-  return lut[probe_edges<6>(a, px, py)];
+  const uint2 V = make_uint2(R.x, R.y), row[6] = {U, U, kNoRow, V, kNoRow, kNoRow};
+  return lut[probe_edges<6>(a, px, py, row)];
 }
 
 // Path-5 (Algorithm 4): v ~ Gamma^(2)_v, u ~ tau^(v) (row prefix ACC_tau), w ~ mu^(v,u)
@@ -2280,7 +2352,8 @@ __device__ __forceinline__ int draw_path5(const SamplerView& a, const uint8_t* l
   }
   if (t == u || r == w || t == r) return 0;
   const int32_t px[6] = {v, v, u, u, w, r}, py[6] = {r, t, w, t, r, t};
-  return lut[probe_edges<6>(a, px, py)];
+  const uint2 V = make_uint2(R.x, R.y), row[6] = {V, V, du >= dw ? U : Wr, U, Wr, kNoRow};
+  return lut[probe_edges<6>(a, px, py, row)];
 }
 
 template <int S>
