@@ -972,40 +972,56 @@ moss_status run_samplers(moss_graph* g, const int* samplers, const uint64_t* k0,
   hipStream_t s = g->stream;
   unsigned long long* d_hits = (unsigned long long*)(g->small + kWHits);
   // XCD-grouped launches sort each chunk of at most 2^25 samples by group (6 bytes per
-  // sample of scratch)
+  // sample of scratch, a block of its own for each sampler)
   void* scratch = nullptr;
   uint64_t max_n = 0;
-  for (int i = 0; i < count; ++i) max_n = std::max<uint64_t>(max_n, k1[i] > k0[i] ? k1[i] - k0[i] : 0);
-  if (grouped_schedule(g, max_n)) {
-    if (fixed) {
-      max_n = std::min<uint64_t>(max_n, fixed_samples);
-      scratch = fixed;
-    } else {
-      max_n = std::min<uint64_t>(max_n, 1ull << 25);
-      if (max_n > 0 && dev_alloc_bytes(s, &scratch, (size_t)grouped_scratch_bytes(max_n)) != MOSS_OK)
-        return MOSS_E_NOMEM;
-    }
+  int samplers_run = 0;
+  for (int i = 0; i < count; ++i) {
+    if (g->total[sampler_slot(samplers[i])] == 0 || k1[i] <= k0[i]) continue;
+    max_n = std::max<uint64_t>(max_n, k1[i] - k0[i]);
+    ++samplers_run;
   }
+  size_t scratch_bytes = 0;
+  if (samplers_run > 0 && grouped_schedule(g, max_n)) {
+    max_n = std::min<uint64_t>(max_n, fixed ? fixed_samples : 1ull << 25);
+    scratch_bytes = (size_t)grouped_scratch_bytes(max_n);
+    scratch = fixed;
+    if (!fixed && samplers_run == 2 && dev_alloc_bytes(s, &scratch, 2 * scratch_bytes) != MOSS_OK) samplers_run = 1;
+    if (!scratch && dev_alloc_bytes(s, &scratch, scratch_bytes) != MOSS_OK) return MOSS_E_NOMEM;
+  }
+  const int step = samplers_run == 2 ? count : 1;  // with one block only, one sampler after the other
   // (with a scratch block, every launch below runs grouped; chunks of at most max_n)
   const uint32_t window = sort_window_for(g);
   hipError_t e = launch_fill_u64(g->small + kWHits, 0, 2 * 22, s);
   if (e == hipSuccess) e = hipEventRecord(g->ev0, s);
-  for (int i = 0; i < count && e == hipSuccess; ++i) {
-    const int slot = sampler_slot(samplers[i]);
-    if (g->total[slot] == 0 || k1[i] <= k0[i]) continue;
+  for (int i = 0; i < count && e == hipSuccess && !scratch; ++i) {
+    if (g->total[sampler_slot(samplers[i])] == 0 || k1[i] <= k0[i]) continue;
     int grid, block;
     plain_launch_shape(g, samplers[i], k1[i] - k0[i], &grid, &block);
-    const SamplerView view = sampler_view(g, samplers[i]);
-    if (!scratch) {
-      e = launch_sample(samplers[i], view, seed, k0[i], k1[i], d_hits + 22 * i, class_out, grid, block, s);
-      continue;
-    }
-    for (uint64_t a = k0[i]; a < k1[i] && e == hipSuccess; a += max_n) {
-      const uint64_t n = std::min<uint64_t>(max_n, k1[i] - a);
-      e = launch_group_chunk(samplers[i], seed, a, n, scratch, max_n, s);
-      if (e == hipSuccess)
-        e = launch_sample_chunk(samplers[i], view, seed, a, n, scratch, max_n, window, d_hits + 22 * i,
-                                class_out ? class_out + (a - k0[i]) : nullptr, grid, block, s);
+    e = launch_sample(samplers[i], sampler_view(g, samplers[i]), seed, k0[i], k1[i], d_hits + 22 * i, class_out, grid,
+                      block, s);
+  }
+  for (int first = 0; first < count && scratch && e == hipSuccess; first += step) {
+    for (uint64_t done = 0; e == hipSuccess; done += max_n) {  // chunk by chunk
+      GroupChunk chunk[2];
+      int which[2], chunks = 0;
+      for (int i = first; i < first + step; ++i) {
+        if (g->total[sampler_slot(samplers[i])] == 0 || k1[i] <= k0[i] || k1[i] - k0[i] <= done) continue;
+        const uint64_t a = k0[i] + done;
+        chunk[chunks] = {samplers[i], seed, a, std::min<uint64_t>(max_n, k1[i] - a),
+                         static_cast<char*>(scratch) + (size_t)chunks * scratch_bytes, max_n};
+        which[chunks++] = i;
+      }
+      if (chunks == 0) break;
+      e = launch_group_chunks(chunk, chunks, s);
+      for (int c = 0; c < chunks && e == hipSuccess; ++c) {
+        const int i = which[c];
+        int grid, block;
+        plain_launch_shape(g, samplers[i], k1[i] - k0[i], &grid, &block);
+        e = launch_sample_chunk(samplers[i], sampler_view(g, samplers[i]), seed, chunk[c].a, chunk[c].n,
+                                chunk[c].scratch, max_n, window, d_hits + 22 * i,
+                                class_out ? class_out + done : nullptr, grid, block, s);
+      }
     }
   }
   if (e == hipSuccess) e = hipEventRecord(g->ev1, s);

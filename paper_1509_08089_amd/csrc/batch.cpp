@@ -417,7 +417,8 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
     if (e != hipSuccess) break;
     const int j = chains == 2 && load[1] < load[0] ? 1 : 0;
     load[j] += chunk_cost(c);
-    e = launch_group_chunk(c.sampler, c.seed, c.a, c.n, sort_scratch_block[j], max_chunk, side_[j]);
+    const GroupChunk one{c.sampler, c.seed, c.a, c.n, sort_scratch_block[j], max_chunk};
+    e = launch_group_chunks(&one, 1, side_[j]);
     if (e == hipSuccess)
       e = launch_sample_chunk(c.sampler, c.view, c.seed, c.a, c.n, sort_scratch_block[j], max_chunk, c.window,
                               d_bins_ + (uint64_t)c.slot * 22, nullptr, c.grid, c.block, side_[j]);

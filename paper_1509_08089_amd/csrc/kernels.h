@@ -238,8 +238,9 @@ hipError_t launch_sample(int sampler, const SamplerView& v, uint64_t seed, uint6
 
 // The same samples drawn XCD-grouped, one chunk [a, a + n) at a time (n <= max_n <=
 // 2^26): the grouping passes (group of each sample, per-block group counts, their scan,
-// the sorted order) into `scratch`, which holds grouped_scratch_bytes(max_n) bytes, then
-// the sampling launch that reads them.  The two may run on different streams, ordered by
+// the sorted order) into `scratch`, which holds grouped_scratch_bytes(max_n) bytes (two
+// chunks with a scratch block each go in the same launches), then the sampling launch that
+// reads them.  The two may run on different streams, ordered by
 // events; a scratch block serves one chunk at a time.  block must be 64, 128, 192 or 256
 // threads; class_out (may be null) receives the chunk's classes at [0, n).
 // `window`: sorted entries a block takes at a time (sort_window of the bytes the
@@ -255,8 +256,13 @@ constexpr uint64_t kFixedScratchBytes = 32ull << 20;
 hipError_t fixed_scratch(int device, void** out);
 std::mutex& fixed_scratch_lock(int device);
 uint32_t sort_window(uint64_t footprint_bytes);
-hipError_t launch_group_chunk(int sampler, uint64_t seed, uint64_t a, uint64_t n, void* scratch, uint64_t max_n,
-                              hipStream_t s);
+struct GroupChunk {
+  int sampler;
+  uint64_t seed, a, n;
+  void* scratch;
+  uint64_t max_n;
+};
+hipError_t launch_group_chunks(const GroupChunk* chunks, int count, hipStream_t s);  // one or two
 hipError_t launch_sample_chunk(int sampler, const SamplerView& v, uint64_t seed, uint64_t a, uint64_t n,
                                void* scratch, uint64_t max_n, uint32_t window, unsigned long long* hits,
                                uint8_t* class_out, int grid, int block, hipStream_t s);

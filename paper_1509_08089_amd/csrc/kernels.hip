@@ -2570,32 +2570,43 @@ constexpr uint32_t kCursorStride = 64;  // u32
 constexpr int kMaxWindow = 512;         // sorted entries a block takes at a time, at most
 
 // The (block, group) count table is stored block-major, one 4 KB row per block, so that
-// the grouping pass writes and the sorting pass reads whole rows.  Its group-major
-// prefix (the place of each (block, group) run in the sorted order) is taken column by
-// column: the rows are cut into at most kSortRuns runs of consecutive blocks, each run
-// sums its rows per group, one wave per four groups scans those sums across the runs,
-// and each run then walks its rows again writing places.  All counts fit 32 bits (a
-// chunk has at most 2^26 samples).  Against a group-major table of 64-bit inclusive
-// counts (one strided 8-byte store and load per (block, group), through the general
-// three-kernel scan): n = 1e5, m = 1e6, MOSS-4 for 1e7 samples, sampling launch 0.493
-// -> 0.476 ms; n = 1e6, m = 1e7, T-5 / Path-5 for 5e7 samples each, 5.58 / 7.57 ->
-// 5.49 / 7.47 ms.
-constexpr uint32_t kSortRuns = 64;  // at most one run per lane of the scanning wave
-constexpr uint32_t kSortQuads = kSortGroups / 4;
-static_assert(kSortQuads == 256, "one group quad per thread of a 256-thread block");
+// the grouping pass writes and the sorting pass reads whole rows.  k_sort_scan turns it
+// into places column by column: a block takes 16 groups (64 bytes of every row), 256
+// row-lanes of four groups each sum a run of rows, the block scans those sums and the
+// row-lanes walk their rows again writing each (block, group) run's place within its
+// group, and the group's total.  The sorting pass's blocks scan the 1024 totals
+// themselves.  All counts fit 32 bits (a chunk has at most 2^26 samples).
+//
+// These passes are short next to a launch, so they go in three launches, and an estimate's
+// two samplers share them (grid.y).  Their blocks have 1024 threads: a chunk of 2e6 samples
+// has 245 blocks, and with 256 threads each SIMD held one wave that waited out its own
+// Philox chain.  Against runs summed, scanned and placed by three kernels (4.7 us each)
+// and one sampler after the other: MOSS-4 with MOSS-4Min for 4e6 samples at n = 3e5,
+// m = 3e6 453 -> 407 us an estimate; n = 1e5, m = 1e6, MOSS-4 for 1e7 samples 428 -> 418 us.
+constexpr int kSortThreads = 1024;
+constexpr uint32_t kScanGroups = 16;   // groups per block of k_sort_scan, four to a row-lane
+constexpr uint32_t kScanQuads = kScanGroups / 4;
+constexpr uint32_t kRowLanes = kSortThreads / kScanQuads;
+static_assert(kSortGroups == kSortThreads, "one group per thread of the sorting pass");
 
 struct SortScratch {
   uint16_t* key;      // n: top 16 bits of each sample's first word (group, then lane bits)
   uint32_t* order;    // n: sample offsets sorted by group, lane bits above them
   uint32_t* counts;   // nblk rows of kSortGroups: block b's count of group g at b * kSortGroups + g
-  uint32_t* place;    // same layout: where run (b, g) starts in the sorted order
-  uint32_t* rsum;     // kSortRuns rows of kSortGroups: per (run, group) sums, then their exclusive prefix
+  uint32_t* place;    // same layout: where run (b, g) starts within group g
   uint32_t* gtot;     // kSortGroups: samples per group
   uint32_t* gstart;   // kSortGroups + 1: start of each group in the sorted order (the last is n)
   uint32_t* cursors;  // kXcds window cursors, kCursorStride apart
   uint32_t nblk;      // blocks (rows) of this chunk
-  uint32_t rows;      // rows per run
-  uint32_t runs;      // runs, <= kSortRuns
+};
+
+// A chunk to group: samples [k0, k0 + n) of the sampler with Philox tag `tag`.
+struct SortJob {
+  uint64_t seed, tag, k0, n;
+  SortScratch t;
+};
+struct SortJobs {
+  SortJob job[2];
 };
 
 __device__ __forceinline__ uint4* quad_at(uint32_t* table, uint32_t row, uint32_t q) {
@@ -2609,11 +2620,7 @@ __device__ __forceinline__ void add4(uint4& a, const uint4& b) {
   a.w += b.w;
 }
 
-static void set_runs(SortScratch& t, uint64_t n) {
-  t.nblk = (uint32_t)std::max<uint64_t>(1, (n + kSortSpan - 1) / kSortSpan);
-  t.rows = (t.nblk + kSortRuns - 1) / kSortRuns;
-  t.runs = (t.nblk + t.rows - 1) / t.rows;
-}
+static uint32_t sort_blocks(uint64_t n) { return (uint32_t)std::max<uint64_t>(1, (n + kSortSpan - 1) / kSortSpan); }
 
 static SortScratch sort_scratch(void* base, uint64_t max_n) {
   SortScratch t;
@@ -2623,12 +2630,11 @@ static SortScratch sort_scratch(void* base, uint64_t max_n) {
     p += (bytes + 255) / 256 * 256;
     return q;
   };
-  set_runs(t, max_n);
+  t.nblk = sort_blocks(max_n);
   t.key = reinterpret_cast<uint16_t*>(take(max_n * 2));
   t.order = reinterpret_cast<uint32_t*>(take(max_n * 4));
   t.counts = reinterpret_cast<uint32_t*>(take((size_t)kSortGroups * t.nblk * 4));
   t.place = reinterpret_cast<uint32_t*>(take((size_t)kSortGroups * t.nblk * 4));
-  t.rsum = reinterpret_cast<uint32_t*>(take((size_t)kSortGroups * kSortRuns * 4));
   t.gtot = reinterpret_cast<uint32_t*>(take((size_t)kSortGroups * 4));
   t.gstart = reinterpret_cast<uint32_t*>(take((size_t)(kSortGroups + 1) * 4));
   t.cursors = reinterpret_cast<uint32_t*>(take(kXcds * kCursorStride * 4));
@@ -2639,7 +2645,7 @@ constexpr uint64_t scratch_bytes_for(uint64_t max_n) {
   const uint64_t nblk = std::max<uint64_t>(1, (max_n + kSortSpan - 1) / kSortSpan);
   auto r = [](uint64_t b) { return (b + 255) / 256 * 256; };
   return r(max_n * 2) + r(max_n * 4) + 2 * r(kSortGroups * nblk * 4) +
-         r(kSortGroups * kSortRuns * 4) + r(kSortGroups * 4) + r((kSortGroups + 1) * 4) +
+         r(kSortGroups * 4) + r((kSortGroups + 1) * 4) +
          r(kXcds * kCursorStride * 4) + 256;
 }
 
@@ -2685,88 +2691,66 @@ std::mutex& fixed_scratch_lock(int device) { return g_fixed_use[device]; }
 
 // Block b counts the groups of samples [b * kSortSpan, (b + 1) * kSortSpan) into row b
 // of the count table.
-template <int S>
-__global__ __launch_bounds__(256) void k_sort_count(uint64_t seed, uint64_t k0, uint64_t n, SortScratch t) {
+__global__ __launch_bounds__(kSortThreads) void k_sort_count(SortJobs jobs) {
   __shared__ uint32_t hist[kSortGroups];
+  const SortJob& job = jobs.job[blockIdx.y];
+  const SortScratch& t = job.t;
+  if (blockIdx.x >= t.nblk) return;  // whole blocks: the other job has more rows
   if (blockIdx.x == 0 && threadIdx.x < kXcds) t.cursors[threadIdx.x * kCursorStride] = 0;
-  for (int g = threadIdx.x; g < kSortGroups; g += blockDim.x) hist[g] = 0;
+  hist[threadIdx.x] = 0;
   __syncthreads();
   const uint64_t lo = (uint64_t)blockIdx.x * kSortSpan;
-  const uint64_t hi = n < lo + kSortSpan ? n : lo + kSortSpan;
-  for (uint64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
+  const uint64_t hi = job.n < lo + kSortSpan ? job.n : lo + kSortSpan;
+  for (uint64_t i = lo + threadIdx.x; i < hi; i += kSortThreads) {
     uint64_t W[4];
-    philox_block(k0 + i, 0, seed, S, W);
+    philox_block(job.k0 + i, 0, job.seed, job.tag, W);
     const uint32_t key = (uint32_t)(W[0] >> 48);
     t.key[i] = (uint16_t)key;
     atomicAdd(&hist[key >> kLaneBits], 1u);
   }
   __syncthreads();
-  for (int g = threadIdx.x; g < kSortGroups; g += blockDim.x) t.counts[(size_t)blockIdx.x * kSortGroups + g] = hist[g];
+  t.counts[(size_t)blockIdx.x * kSortGroups + threadIdx.x] = hist[threadIdx.x];
 }
 
-// Run r sums rows [r * rows, (r + 1) * rows) of the count table per group.  The rows'
-// loads go out 16 at a time.
-__global__ __launch_bounds__(256) void k_sort_runsum(SortScratch t) {
-  const uint32_t q = threadIdx.x;  // blockDim.x == kSortQuads
-  const uint32_t b0 = blockIdx.x * t.rows, b1 = min(t.nblk, b0 + t.rows);
-  uint4 s = make_uint4(0, 0, 0, 0);
-  for (uint32_t b = b0; b < b1; b += 16) {
-    uint4 c[16];
+// Block x takes groups [16 x, 16 x + 16): the place of every (block, group) run within its
+// group, and the groups' totals.  Row-lane r (threads 4 r .. 4 r + 3) walks a run of rows.
+__global__ __launch_bounds__(kSortThreads) void k_sort_scan(SortJobs jobs) {
+  __shared__ uint4 wsum[kSortThreads / 64][kScanQuads];
+  const SortScratch& t = jobs.job[blockIdx.y].t;
+  const uint32_t q = blockIdx.x * kScanQuads + threadIdx.x % kScanQuads, r = threadIdx.x / kScanQuads;
+  const uint32_t rows = (t.nblk + kRowLanes - 1) / kRowLanes;
+  const uint32_t b0 = min(t.nblk, r * rows), b1 = min(t.nblk, b0 + rows);
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  uint4 sum = make_uint4(0, 0, 0, 0);
+  for (uint32_t b = b0; b < b1; b += 8) {  // eight loads in flight
+    uint4 c[8];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) c[k] = b + k < b1 ? *quad_at(t.counts, b + k, q) : make_uint4(0, 0, 0, 0);
+    for (int k = 0; k < 8; ++k) c[k] = b + k < b1 ? *quad_at(t.counts, b + k, q) : make_uint4(0, 0, 0, 0);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) add4(s, c[k]);
+    for (int k = 0; k < 8; ++k) add4(sum, c[k]);
   }
-  *quad_at(t.rsum, blockIdx.x, q) = s;
-}
-
-// One wave per four groups: lane r holds run r's sums and the wave scans them, leaving
-// each run's exclusive prefix in place and the groups' totals in gtot.  Two 32-bit sums
-// share a 64-bit lane value; neither half carries into the other, since every sum is at
-// most the chunk's sample count (< 2^32).
-__global__ __launch_bounds__(256) void k_sort_runscan(SortScratch t) {
-  const uint32_t q = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), r = (uint32_t)lane_id();
-  if (q >= kSortQuads) return;  // whole waves
-  const uint4 v = r < t.runs ? *quad_at(t.rsum, r, q) : make_uint4(0, 0, 0, 0);
-  const uint64_t lo = (uint64_t)v.x | ((uint64_t)v.y << 32), hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
-  bool unused = false;
-  const uint64_t ilo = wave_inclusive_scan(lo, unused), ihi = wave_inclusive_scan(hi, unused);
-  const uint64_t elo = ilo - lo, ehi = ihi - hi;
-  if (r < t.runs)
-    *quad_at(t.rsum, r, q) = make_uint4((uint32_t)elo, (uint32_t)(elo >> 32), (uint32_t)ehi, (uint32_t)(ehi >> 32));
-  if (r == t.runs - 1)
-    *quad_at(t.gtot, 0, q) = make_uint4((uint32_t)ilo, (uint32_t)(ilo >> 32), (uint32_t)ihi, (uint32_t)(ihi >> 32));
-}
-
-// Each run block first turns the group totals into group starts (a block scan; block 0
-// stores them, with n after the last), then walks its rows: the place of run (b, g) is
-// g's start, plus the samples of g in earlier runs, plus those in the run's earlier rows.
-__global__ __launch_bounds__(256) void k_sort_place(uint64_t n, SortScratch t) {
-  __shared__ uint32_t wsum[4];
-  const uint32_t q = threadIdx.x;  // blockDim.x == kSortQuads
-  const int lane = lane_id(), wave = (int)(q >> 6);
-  const uint4 tot = *quad_at(t.gtot, 0, q);
-  const uint32_t mine = tot.x + tot.y + tot.z + tot.w;
-  bool unused = false;
-  const uint32_t incl = (uint32_t)wave_inclusive_scan((uint64_t)mine, unused);
-  if (lane == 63) wsum[wave] = incl;
+  // inclusive scan over the row-lanes: within the wave, then over the waves before
+  uint4 incl = sum;
+#pragma unroll
+  for (int off = kScanQuads; off < 64; off *= 2) {
+    uint4 y;
+    y.x = __shfl_up(incl.x, off, 64);
+    y.y = __shfl_up(incl.y, off, 64);
+    y.z = __shfl_up(incl.z, off, 64);
+    y.w = __shfl_up(incl.w, off, 64);
+    if (lane >= off) add4(incl, y);
+  }
+  if (lane >= 64 - (int)kScanQuads) wsum[wave][lane % kScanQuads] = incl;
   __syncthreads();
-  uint32_t off = incl - mine;
-  for (int w = 0; w < wave; ++w) off += wsum[w];
-  const uint4 start = make_uint4(off, off + tot.x, off + tot.x + tot.y, off + tot.x + tot.y + tot.z);
-  if (blockIdx.x == 0) {
-    *quad_at(t.gstart, 0, q) = start;
-    if (q == 0) t.gstart[kSortGroups] = (uint32_t)n;
-  }
-  uint4 run = *quad_at(t.rsum, blockIdx.x, q);
-  add4(run, start);
-  const uint32_t b0 = blockIdx.x * t.rows, b1 = min(t.nblk, b0 + t.rows);
-  for (uint32_t b = b0; b < b1; b += 16) {
-    uint4 c[16];
+  for (int w = 0; w < wave; ++w) add4(incl, wsum[w][lane % kScanQuads]);
+  if (r == kRowLanes - 1) *quad_at(t.gtot, 0, q) = incl;
+  uint4 run = make_uint4(incl.x - sum.x, incl.y - sum.y, incl.z - sum.z, incl.w - sum.w);
+  for (uint32_t b = b0; b < b1; b += 8) {
+    uint4 c[8];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) c[k] = b + k < b1 ? *quad_at(t.counts, b + k, q) : make_uint4(0, 0, 0, 0);
+    for (int k = 0; k < 8; ++k) c[k] = b + k < b1 ? *quad_at(t.counts, b + k, q) : make_uint4(0, 0, 0, 0);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
+    for (int k = 0; k < 8; ++k) {
       if (b + k < b1) {
         *quad_at(t.place, b + k, q) = run;
         add4(run, c[k]);
@@ -2775,62 +2759,55 @@ __global__ __launch_bounds__(256) void k_sort_place(uint64_t n, SortScratch t) {
   }
 }
 
-// The same blocks place their samples.  A block first sorts its span by group in LDS
-// (a sample of group g takes the next free slot of g's run), then writes each run to
-// the block's share of g in the sorted order: consecutive threads write consecutive
-// slots, so the stores coalesce (slot order within a share is immaterial).  The group
-// bytes come in 16-byte loads and the local order is kept as 16-bit offsets (27 KB of
-// LDS a block instead of 43 KB): 69 -> 37 us a pass on average over the n = 1e5,
-// m = 1e6 and n = 1e6, m = 1e7 workloads.
-__global__ __launch_bounds__(256) void k_sort_scatter(uint64_t n, SortScratch t) {
-  constexpr int kPerThread = kSortGroups / 256;  // thread tid owns groups tid * kPerThread ..
-  __shared__ uint32_t base[kSortGroups];   // per group: the block's share in the sorted order
-  __shared__ uint32_t start[kSortGroups];  // per group: the run's start in the local order
+// The same blocks as the counting pass place their samples; thread g looks after group g.
+// A block first sorts its span by group in LDS (a sample of group g takes the next free
+// slot of g's run), then writes each run to the block's share of g in the sorted order:
+// consecutive threads write consecutive slots, so the stores coalesce (slot order within a
+// share is immaterial).  Block 0 also stores the groups' starts, n after the last.
+__global__ __launch_bounds__(kSortThreads) void k_sort_scatter(SortJobs jobs) {
+  __shared__ uint32_t delta[kSortGroups];  // per group: the block's share's start less the run's local start
   __shared__ uint32_t next[kSortGroups];   // per group: the run's fill cursor
-  __shared__ uint32_t wsum[4];
+  __shared__ uint64_t wsum[kSortThreads / 64];
   __shared__ uint16_t local[kSortSpan];    // span offsets sorted by group
   __shared__ __align__(16) uint16_t key[kSortSpan];
-  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;  // blockDim.x == 256
+  const SortJob& job = jobs.job[blockIdx.y];
+  const SortScratch& t = job.t;
+  if (blockIdx.x >= t.nblk) return;  // whole blocks
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   const uint64_t lo = (uint64_t)blockIdx.x * kSortSpan;
-  const uint32_t len = (uint32_t)(n < lo + kSortSpan ? n - lo : kSortSpan);
-  // the block's share of each of this thread's groups: its place and its size
-  uint32_t size[kPerThread];
-  uint32_t mine = 0;
-#pragma unroll
-  for (int j = 0; j < kPerThread; ++j) {
-    const uint32_t g = (uint32_t)tid * kPerThread + j;
-    const size_t idx = (size_t)blockIdx.x * kSortGroups + g;
-    base[g] = t.place[idx];
-    size[j] = t.counts[idx];
-    mine += size[j];
-  }
+  const uint32_t len = (uint32_t)(job.n < lo + kSortSpan ? job.n - lo : kSortSpan);
+  const size_t at = (size_t)blockIdx.x * kSortGroups + tid;
+  const uint32_t size = t.counts[at], total = t.gtot[tid];
+  const uint32_t place = t.place[at];
   if (len == kSortSpan) {  // whole span: 16-byte loads
-    for (uint32_t j = tid; j < kSortSpan * 2 / 16; j += blockDim.x)
-      reinterpret_cast<uint4*>(key)[j] = reinterpret_cast<const uint4*>(t.key + lo)[j];
+    static_assert(kSortSpan * 2 / 16 == kSortThreads, "one load a thread");
+    reinterpret_cast<uint4*>(key)[tid] = reinterpret_cast<const uint4*>(t.key + lo)[tid];
   } else {
-    for (uint32_t j = tid; j < len; j += blockDim.x) key[j] = t.key[lo + j];
+    for (uint32_t j = tid; j < len; j += kSortThreads) key[j] = t.key[lo + j];
   }
-  // exclusive prefix of the share sizes in group order: local run starts
+  // exclusive prefixes over the groups: of the block's sizes (low half; the runs' local
+  // starts) and of the totals (high half; the groups' starts), neither past 2^26
+  const uint64_t both = (uint64_t)total << 32 | size;
   bool unused = false;
-  const uint32_t incl = (uint32_t)wave_inclusive_scan((uint64_t)mine, unused);
+  uint64_t incl = wave_inclusive_scan(both, unused);
   if (lane == 63) wsum[wave] = incl;
   __syncthreads();
-  uint32_t off = incl - mine;
-  for (int w = 0; w < wave; ++w) off += wsum[w];
-#pragma unroll
-  for (int j = 0; j < kPerThread; ++j) {
-    const uint32_t g = (uint32_t)tid * kPerThread + j;
-    start[g] = off;
-    next[g] = off;
-    off += size[j];
+  for (int w = 0; w < wave; ++w) incl += wsum[w];
+  const uint64_t before = incl - both;
+  const uint32_t start = (uint32_t)before, gstart = (uint32_t)(before >> 32);
+  next[tid] = start;
+  delta[tid] = gstart + place - start;
+  if (blockIdx.x == 0) {
+    t.gstart[tid] = gstart;
+    if (tid == 0) t.gstart[kSortGroups] = (uint32_t)job.n;
   }
   __syncthreads();
-  for (uint32_t j = tid; j < len; j += blockDim.x) local[atomicAdd(&next[key[j] >> kLaneBits], 1u)] = (uint16_t)j;
+  for (uint32_t j = tid; j < len; j += kSortThreads) local[atomicAdd(&next[key[j] >> kLaneBits], 1u)] = (uint16_t)j;
   __syncthreads();
-  for (uint32_t j = tid; j < len; j += blockDim.x) {
+  for (uint32_t j = tid; j < len; j += kSortThreads) {
     const uint32_t o = local[j];
-    const uint32_t k = key[o], g = k >> kLaneBits;
-    t.order[(uint64_t)base[g] + (j - start[g])] = (uint32_t)(lo + o) | (k << kOrderBits);
+    const uint32_t k = key[o];
+    t.order[delta[k >> kLaneBits] + j] = (uint32_t)(lo + o) | (k << kOrderBits);
   }
 }
 
@@ -2901,23 +2878,25 @@ __global__ __launch_bounds__(256, kSampleWaves) void k_sample_sorted(SamplerView
   }
 }
 
-hipError_t launch_group_chunk(int sampler, uint64_t seed, uint64_t a, uint64_t n, void* scratch, uint64_t max_n,
-                              hipStream_t s) {
-  if (n == 0 || n > max_n || max_n > (1ull << kOrderBits)) return hipErrorInvalidValue;
-  SortScratch tc = sort_scratch(scratch, max_n);
-  set_runs(tc, n);
-  const uint32_t nblk = tc.nblk;
-  switch (sampler) {
-    case kMoss4: hipLaunchKernelGGL(k_sort_count<kMoss4>, dim3(nblk), dim3(256), 0, s, seed, a, n, tc); break;
-    case kMoss4Min: hipLaunchKernelGGL(k_sort_count<kMoss4Min>, dim3(nblk), dim3(256), 0, s, seed, a, n, tc); break;
-    case kT5: hipLaunchKernelGGL(k_sort_count<kT5>, dim3(nblk), dim3(256), 0, s, seed, a, n, tc); break;
-    case kPath5: hipLaunchKernelGGL(k_sort_count<kPath5>, dim3(nblk), dim3(256), 0, s, seed, a, n, tc); break;
-    default: return hipErrorInvalidValue;
+hipError_t launch_group_chunks(const GroupChunk* chunks, int count, hipStream_t s) {
+  if (count < 1 || count > 2) return hipErrorInvalidValue;
+  SortJobs jobs{};
+  uint32_t most = 0;
+  for (int i = 0; i < count; ++i) {
+    const GroupChunk& c = chunks[i];
+    if (c.n == 0 || c.n > c.max_n || c.max_n > (1ull << kOrderBits)) return hipErrorInvalidValue;
+    SortJob& j = jobs.job[i];
+    j.seed = c.seed;
+    j.tag = (uint64_t)c.sampler;
+    j.k0 = c.a;
+    j.n = c.n;
+    j.t = sort_scratch(c.scratch, c.max_n);
+    j.t.nblk = sort_blocks(c.n);
+    most = std::max(most, j.t.nblk);
   }
-  hipLaunchKernelGGL(k_sort_runsum, dim3(tc.runs), dim3(kSortQuads), 0, s, tc);
-  hipLaunchKernelGGL(k_sort_runscan, dim3(kSortQuads / 4), dim3(256), 0, s, tc);
-  hipLaunchKernelGGL(k_sort_place, dim3(tc.runs), dim3(kSortQuads), 0, s, n, tc);
-  hipLaunchKernelGGL(k_sort_scatter, dim3(nblk), dim3(256), 0, s, n, tc);
+  hipLaunchKernelGGL(k_sort_count, dim3(most, count), dim3(kSortThreads), 0, s, jobs);
+  hipLaunchKernelGGL(k_sort_scan, dim3(kSortGroups / kScanGroups, count), dim3(kSortThreads), 0, s, jobs);
+  hipLaunchKernelGGL(k_sort_scatter, dim3(most, count), dim3(kSortThreads), 0, s, jobs);
   return hipGetLastError();
 }
 
@@ -2928,7 +2907,7 @@ hipError_t launch_sample_chunk(int sampler, const SamplerView& v, uint64_t seed,
       max_n > (1ull << kOrderBits) || window == 0 || window > (uint32_t)kMaxWindow)
     return hipErrorInvalidValue;
   SortScratch tc = sort_scratch(scratch, max_n);
-  set_runs(tc, n);
+  tc.nblk = sort_blocks(n);
   // no more blocks than windows (each block visits every cursor once at least), a
   // multiple of the XCD count so that every XCD gets its share of blocks
   const uint64_t wins = (n + window - 1) / window;

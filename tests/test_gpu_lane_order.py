@@ -32,3 +32,19 @@ def test_windows_draw_every_sample_once(graph, window, threads, count):
     np.testing.assert_array_equal(ca, cb)
     np.testing.assert_array_equal(ha, hb)
     np.testing.assert_array_equal(ha, np.bincount(ca, minlength=22))
+
+
+@pytest.mark.parametrize("k,flags", [(4, moss.MOSS_K4_MIN), (5, 0)])
+@pytest.mark.parametrize("n", [2, 3, 16_385, 300 * 16_384 + 1])
+def test_two_samplers_grouped_together(graph, k, flags, n):
+    """An estimate's two samplers share the grouping launches; the first may have a block (and
+    with 300 blocks a row more to a row-lane of the scan) more than the second."""
+    try:
+        moss.moss_set_tuning(schedule=moss.MOSS_SCHEDULE_PLAIN)
+        a = graph.estimate(k, n, 12, flags)
+        moss.moss_set_tuning(schedule=moss.MOSS_SCHEDULE_XCD)
+        b = graph.estimate(k, n, 12, flags)
+    finally:
+        moss.moss_set_tuning()
+    np.testing.assert_array_equal(a.hits_np, b.hits_np)
+    assert b.hits_np[:, :7 if k == 4 else 22].sum() == n
