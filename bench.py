@@ -25,7 +25,7 @@ The same JSON line also carries:
                 the L2s and L2 requests per launch, from the committed rocprofv3 counter
                 summaries of the same command (profiles/counters_<workload>.md, used only
                 when taken on the current kernel sources), over the launch's device time
-                measured live with HIP events on its stream; frac is the larger of
+                measured live (moss_result.device_ms); frac is the larger of
                 fabric bytes/s / 8 TB/s and L2 requests/s / (128 channels x L2 clock)
   gather        the random-gather ceiling: chains of dependent 8-byte loads, several
                 chains per lane, over a buffer the size of the C3 samplers' footprint
@@ -71,10 +71,10 @@ WORKLOAD_TEXT = {
           "k in {4,5}, budgets log-uniform 1e4..1e8, memory-based admission",
 }
 
-# kernels that run between the HIP events bracketing a sampling launch (moss_estimate's
-# grouping passes and sampling kernels; the batched launch's clear, persistent kernel
-# and grouped launches)
-LAUNCH_KERNELS = ("k_sort_count", "k_sort_runsum", "k_sort_runscan", "k_sort_place", "k_sort_scatter",
+# kernels that moss_result.device_ms of a sampling launch covers (moss_estimate's grouping
+# passes and sampling kernels; the batched launch's clear, persistent kernel and grouped
+# launches)
+LAUNCH_KERNELS = ("k_sort_count", "k_sort_scan", "k_sort_scatter",
                   "k_sample_sorted", "k_sample<", "k_batch", "k_fill_u64", "k_fill_u32")
 
 

@@ -151,7 +151,8 @@ typedef struct {
   uint64_t lambda;         /* k=4: Lambda_3; k=5: Lambda_4 */
   double estimate[21];     /* estimate[i-1] of n_i (k=4, i <= 6) or eta_i (k=5) */
   double variance[21];     /* Theorem 3 / Theorem 10 evaluated at the estimates */
-  double device_ms;        /* device time of the sampling kernels (HIP events) */
+  double device_ms;        /* device time of the sampling kernels, by the device's clock
+                              (batched: HIP events around the batch) */
 } moss_result;
 
 /* ---- errors ---------------------------------------------------------------------- */

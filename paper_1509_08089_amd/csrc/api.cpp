@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -41,6 +42,7 @@ namespace {
 std::mutex g_dev_mu;
 std::vector<int> g_dev_ready;  // per device: 0 not set up, 1 ready
 std::vector<int> g_dev_cus;
+std::vector<double> g_dev_ticks_per_ms;
 }  // namespace
 
 moss_status ensure_device(int device) {
@@ -49,6 +51,7 @@ moss_status ensure_device(int device) {
   if ((int)g_dev_ready.size() <= device) {
     g_dev_ready.resize(device + 1, 0);
     g_dev_cus.resize(device + 1, 0);
+    g_dev_ticks_per_ms.resize(device + 1, 0.0);
   }
   if (g_dev_ready[device]) return MOSS_OK;
   DeviceScope scope(device);
@@ -60,12 +63,16 @@ moss_status ensure_device(int device) {
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
     return MOSS_E_DEVICE;
+  int khz = 0;  // of the device clock that wall_clock64() reads
+  if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || khz <= 0)
+    return MOSS_E_DEVICE;
   hipMemPool_t pool = nullptr;
   if (hipDeviceGetDefaultMemPool(&pool, device) == hipSuccess && pool) {
     uint64_t keep = ~0ull;  // keep freed blocks for reuse instead of returning them at each sync
     (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
   }
   g_dev_cus[device] = cus;
+  g_dev_ticks_per_ms[device] = (double)khz;
   g_dev_ready[device] = 1;
   return MOSS_OK;
 }
@@ -73,6 +80,11 @@ moss_status ensure_device(int device) {
 int device_cus(int device) {
   std::lock_guard<std::mutex> lk(g_dev_mu);
   return device >= 0 && device < (int)g_dev_cus.size() && g_dev_cus[device] > 0 ? g_dev_cus[device] : 256;
+}
+
+double device_ticks_per_ms(int device) {
+  std::lock_guard<std::mutex> lk(g_dev_mu);
+  return g_dev_ticks_per_ms[(size_t)device];  // callers hold a graph of the device, so it is set up
 }
 
 SamplerView sampler_view(const moss_graph* g, int sampler) {
@@ -164,23 +176,31 @@ moss_status plan_estimate(int32_t k, uint64_t n_samples, uint32_t flags, Estimat
   return MOSS_OK;
 }
 
-void plain_launch_shape(const moss_graph* g, int sampler, uint64_t nsamples, int* grid, int* block) {
+// The most blocks a launch of the sampler on g has: resident waves by schedule and footprint.
+static int most_blocks(const moss_graph* g, int sampler, bool grouped, int block) {
   const Tuning t = current_tuning();
-  int b = t.threads_per_block ? (int)t.threads_per_block : 256;
-  int per_cu = t.blocks_per_cu ? (int)t.blocks_per_cu : 0;
+  int per_cu = (int)t.blocks_per_cu;
   if (per_cu == 0) {
     // grouped launches: 28 waves per CU (n = 1e5, m = 1e6, MOSS-4 for 1e7 samples,
     // 12 / 16 / 20 / 24 / 28 / 32 waves: 0.687 / 0.602 / 0.559 / 0.542 / 0.538 / 0.540
     // ms; n = 1e6, m = 1e7, T-5 for 5e7: 6.14 / 5.71 / 5.61 / 5.60 / 5.61 / 5.62 ms)
-    const uint64_t fp = sampling_footprint(g);
-    const int waves = grouped_schedule(g, nsamples) ? 28 : sampling_waves_per_cu(fp);
-    const int cap = std::max(1, std::min(sample_kernel_blocks_per_cu(sampler, b), 8));
-    per_cu = std::max(1, std::min(cap, waves / (b / 64)));
+    const int waves = grouped ? 28 : sampling_waves_per_cu(sampling_footprint(g));
+    const int cap = std::max(1, std::min(sample_kernel_blocks_per_cu(sampler, block), 8));
+    per_cu = std::max(1, std::min(cap, waves / (block / 64)));
   }
-  const uint64_t want = (nsamples + (uint64_t)b - 1) / (uint64_t)b;
-  const uint64_t most = (uint64_t)device_cus(g->device) * (uint64_t)per_cu;
+  return device_cus(g->device) * per_cu;
+}
+
+static int threads_per_block() {
+  const Tuning t = current_tuning();
+  return t.threads_per_block ? (int)t.threads_per_block : 256;
+}
+
+void grouped_launch_shape(const moss_graph* g, int sampler, uint64_t nsamples, int* grid, int* block) {
+  *block = threads_per_block();
+  const uint64_t want = (nsamples + (uint64_t)*block - 1) / (uint64_t)*block;
+  const uint64_t most = (uint64_t)most_blocks(g, sampler, grouped_schedule(g, nsamples), *block);
   *grid = (int)std::max<uint64_t>(1, std::min(want, most));
-  *block = b;
 }
 
 }  // namespace moss
@@ -296,7 +316,7 @@ T* at(void* base, size_t off) {
 // per graph: word block, edge hash set and filter, items, item sums, row-guide lengths,
 // scan scratch, partials, records
 struct GraphLayout {
-  size_t small, slots, filter, items, item_sum, guide_len, tmp[3], partials, rec, span_row, check_part, span_sums,
+  size_t small, hit_parts, slots, filter, items, item_sum, guide_len, tmp[3], partials, rec, span_row, check_part, span_sums,
       span_groups, group_wrap, hub_filter, bytes;
 };
 
@@ -305,6 +325,7 @@ GraphLayout graph_layout(int32_t n, int64_t nnz) {
   GraphLayout L;
   Carve c;
   L.small = c.take<uint64_t>(kWords);
+  L.hit_parts = c.take<uint64_t>(kHitPartsWords);
   L.slots = c.take<uint64_t>((size_t)1 << edge_hash_bits(nnz / 2));
   L.filter = c.take<uint64_t>((size_t)1 << edge_filter_bits(nnz / 2));
   L.items = c.take<uint64_t>((size_t)cap);
@@ -402,30 +423,6 @@ void pinned_release(uint64_t* p) {
   g_pin_free.push_back(p);
 }
 
-// Timing events, kept per device for reuse (creating and destroying them costs more
-// than the small calls they time).
-std::vector<std::vector<hipEvent_t>> g_events;  // guarded by g_pin_mu
-
-hipEvent_t pooled_event(int device) {
-  {
-    std::lock_guard<std::mutex> lk(g_pin_mu);
-    if ((int)g_events.size() > device && !g_events[device].empty()) {
-      hipEvent_t e = g_events[device].back();
-      g_events[device].pop_back();
-      return e;
-    }
-  }
-  hipEvent_t e = nullptr;
-  return hipEventCreate(&e) == hipSuccess ? e : nullptr;
-}
-
-void event_release(int device, hipEvent_t e) {
-  if (!e) return;
-  std::lock_guard<std::mutex> lk(g_pin_mu);
-  if ((int)g_events.size() <= device) g_events.resize(device + 1);
-  g_events[device].push_back(e);
-}
-
 void free_tables(moss_graph* g, uint32_t mask) {
   if (mask & MOSS_TABLES_K4) {
     dev_free(g->stream, g->mem_k4);
@@ -470,8 +467,6 @@ void destroy_graph(moss_graph* g) {
   dev_free(g->stream, g->mem_graph);
   pinned_release(g->h_stage);
   g->h_stage = nullptr;
-  event_release(g->device, g->ev0);
-  event_release(g->device, g->ev1);
   delete g;
 }
 
@@ -495,6 +490,7 @@ moss_status finish_create(moss_graph* g) {
   if (st != MOSS_OK) return st;
   void* m = g->mem_graph;
   g->small = at<uint64_t>(m, L.small);
+  g->hit_parts = at<unsigned long long>(m, L.hit_parts);
   g->edge_slots = at<uint64_t>(m, L.slots);
   g->filter = at<uint64_t>(m, L.filter);
   g->edge_bits = edge_hash_bits(g->nnz / 2);
@@ -512,7 +508,6 @@ moss_status finish_create(moss_graph* g) {
   g->group_wrap = at<uint32_t>(m, L.group_wrap);
   g->hub_filter = at<uint64_t>(m, L.hub_filter);
   if (!(g->h_stage = pinned_chunk())) return MOSS_E_NOMEM;
-  if (!(g->ev0 = pooled_event(g->device)) || !(g->ev1 = pooled_event(g->device))) return MOSS_E_DEVICE;
   hipStream_t s = g->stream;
   const int64_t cap = items_cap(g->n, g->nnz);
   uint32_t* err = (uint32_t*)(g->small + kWErr);
@@ -524,6 +519,8 @@ moss_status finish_create(moss_graph* g) {
   f.value[1] = ~0ull;
   f.p[2] = g->filter;
   f.count[2] = (int64_t)1 << g->filter_bits;
+  f.p[3] = (uint64_t*)g->hit_parts;
+  f.count[3] = kHitPartsWords;
   hipError_t e = launch_fill_set(f, s);
   // item_sum holds the piece counts here, scanned into each row's item end
   if (e == hipSuccess) e = launch_node_prep(g->n, g->nnz, g->rp, g->item_sum, g->guide_len, g->small, s);
@@ -916,7 +913,7 @@ moss_status moss::build_tables(moss_graph* g, uint32_t k_mask) {
     if (e == hipSuccess) e = launch_guides(mg, g->n, g->gbits, s);
   }
   uint64_t* h = g->h_stage;
-  if (e == hipSuccess) e = hipMemcpyAsync(h, g->small, kWHits * sizeof(uint64_t), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(h, g->small, kWBack * sizeof(uint64_t), hipMemcpyDeviceToHost, s);
   const hipError_t es = hipStreamSynchronize(s);  // also drains work queued before a failed launch
   if (e == hipSuccess) e = es;
   if (e != hipSuccess) {
@@ -970,16 +967,23 @@ moss_status run_samplers(moss_graph* g, const int* samplers, const uint64_t* k0,
                          uint64_t seed, uint8_t* class_out, uint64_t hits[][22], double* device_ms,
                          void* fixed = nullptr, uint64_t fixed_samples = 0) {
   hipStream_t s = g->stream;
-  unsigned long long* d_hits = (unsigned long long*)(g->small + kWHits);
   // XCD-grouped launches sort each chunk of at most 2^25 samples by group (6 bytes per
   // sample of scratch, a block of its own for each sampler)
   void* scratch = nullptr;
   uint64_t max_n = 0;
-  int samplers_run = 0;
+  int samplers_run = 0;  // samplers that draw something
+  auto draws = [&](int i) { return g->total[sampler_slot(samplers[i])] != 0 && k1[i] > k0[i]; };
   for (int i = 0; i < count; ++i) {
-    if (g->total[sampler_slot(samplers[i])] == 0 || k1[i] <= k0[i]) continue;
+    if (!draws(i)) continue;
     max_n = std::max<uint64_t>(max_n, k1[i] - k0[i]);
     ++samplers_run;
+  }
+  if (samplers_run == 0) {
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return status_of(e);
+    for (int i = 0; i < count; ++i) std::memset(hits[i], 0, 22 * sizeof(uint64_t));
+    if (device_ms) *device_ms = 0.0;
+    return MOSS_OK;
   }
   size_t scratch_bytes = 0;
   if (samplers_run > 0 && grouped_schedule(g, max_n)) {
@@ -992,48 +996,84 @@ moss_status run_samplers(moss_graph* g, const int* samplers, const uint64_t* k0,
   const int step = samplers_run == 2 ? count : 1;  // with one block only, one sampler after the other
   // (with a scratch block, every launch below runs grouped; chunks of at most max_n)
   const uint32_t window = sort_window_for(g);
-  hipError_t e = launch_fill_u64(g->small + kWHits, 0, 2 * 22, s);
-  if (e == hipSuccess) e = hipEventRecord(g->ev0, s);
-  for (int i = 0; i < count && e == hipSuccess && !scratch; ++i) {
-    if (g->total[sampler_slot(samplers[i])] == 0 || k1[i] <= k0[i]) continue;
-    int grid, block;
-    plain_launch_shape(g, samplers[i], k1[i] - k0[i], &grid, &block);
-    e = launch_sample(samplers[i], sampler_view(g, samplers[i]), seed, k0[i], k1[i], d_hits + 22 * i, class_out, grid,
-                      block, s);
+  HitSink sink{};
+  sink.parts = g->hit_parts;
+  sink.seq = ++g->host_seq;
+  sink.first = 1;
+  auto* host = (unsigned long long*)g->h_stage;
+  host[kHostSeq] = 0;  // no launch of an earlier call still writes here
+  hipError_t e = hipSuccess;
+  if (!scratch) {
+    PlainLaunch l{};
+    l.seed = seed;
+    l.block = threads_per_block();
+    for (int i = 0; i < count; ++i) {
+      if (!draws(i)) continue;
+      if (l.count == 0) sink.base = 22u * (uint32_t)i;
+      l.sampler[l.count] = samplers[i];
+      l.view[l.count] = sampler_view(g, samplers[i]);
+      l.k0[l.count] = k0[i];
+      l.k1[l.count] = k1[i];
+      l.most_blocks = std::max(l.most_blocks, most_blocks(g, samplers[i], false, l.block));
+      ++l.count;
+    }
+    sink.host = host;
+    e = launch_sample(l, sink, class_out, s);
   }
+  uint64_t launches = 0;  // sampling launches of the grouped form
+  for (int i = 0; i < count && scratch; ++i)
+    if (draws(i)) launches += (k1[i] - k0[i] + max_n - 1) / max_n;
+  bool started = false;
   for (int first = 0; first < count && scratch && e == hipSuccess; first += step) {
     for (uint64_t done = 0; e == hipSuccess; done += max_n) {  // chunk by chunk
       GroupChunk chunk[2];
       int which[2], chunks = 0;
       for (int i = first; i < first + step; ++i) {
-        if (g->total[sampler_slot(samplers[i])] == 0 || k1[i] <= k0[i] || k1[i] - k0[i] <= done) continue;
+        if (!draws(i) || k1[i] - k0[i] <= done) continue;
         const uint64_t a = k0[i] + done;
         chunk[chunks] = {samplers[i], seed, a, std::min<uint64_t>(max_n, k1[i] - a),
                          static_cast<char*>(scratch) + (size_t)chunks * scratch_bytes, max_n};
         which[chunks++] = i;
       }
       if (chunks == 0) break;
-      e = launch_group_chunks(chunk, chunks, s);
+      e = launch_group_chunks(chunk, chunks, started ? nullptr : sink.parts, s);
+      started = true;
       for (int c = 0; c < chunks && e == hipSuccess; ++c) {
         const int i = which[c];
         int grid, block;
-        plain_launch_shape(g, samplers[i], k1[i] - k0[i], &grid, &block);
+        grouped_launch_shape(g, samplers[i], k1[i] - k0[i], &grid, &block);
+        sink.first = 0;
+        sink.base = 22u * (uint32_t)i;
+        sink.host = --launches == 0 ? host : nullptr;  // the call's last launch hands the counts over
         e = launch_sample_chunk(samplers[i], sampler_view(g, samplers[i]), seed, chunk[c].a, chunk[c].n,
-                                chunk[c].scratch, max_n, window, d_hits + 22 * i,
-                                class_out ? class_out + done : nullptr, grid, block, s);
+                                chunk[c].scratch, max_n, window, sink, class_out ? class_out + done : nullptr, grid,
+                                block, s);
       }
     }
   }
-  if (e == hipSuccess) e = hipEventRecord(g->ev1, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(g->h_stage, d_hits, 2 * 22 * sizeof(uint64_t), hipMemcpyDeviceToHost, s);
-  const hipError_t es = hipStreamSynchronize(s);
-  if (e == hipSuccess) e = es;
+  // The counts are in host memory once the sequence number is.  Waiting for that alone is 3 us
+  // shorter than for the stream; a scratch block goes back, and classes to the caller, only
+  // when the stream has drained.
+  bool there = false;
+  if (e == hipSuccess && !scratch && !class_out) {
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+    do {
+      for (int i = 0; i < 64 && !there; ++i) there = __atomic_load_n(&host[kHostSeq], __ATOMIC_ACQUIRE) == sink.seq;
+    } while (!there && std::chrono::steady_clock::now() < until);
+  }
+  if (!there) {
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
+    there = e == hipSuccess && __atomic_load_n(&host[kHostSeq], __ATOMIC_ACQUIRE) == sink.seq;
+  }
   if (scratch != fixed) dev_free(s, scratch);  // idle after the synchronisation
-  if (e != hipSuccess) return status_of(e);
+  if (!there) {  // the next call finds no counts of a launch that did go out
+    (void)launch_fill_u64((uint64_t*)g->hit_parts, 0, kHitPartsWords, s);
+    (void)hipStreamSynchronize(s);
+    return e == hipSuccess ? MOSS_E_DEVICE : status_of(e);
+  }
   for (int i = 0; i < count; ++i) std::memcpy(hits[i], g->h_stage + 22 * i, 22 * sizeof(uint64_t));
-  float ms = 0.f;
-  if (device_ms) *device_ms = hipEventElapsedTime(&ms, g->ev0, g->ev1) == hipSuccess ? (double)ms : 0.0;
+  if (device_ms) *device_ms = (double)host[kHostTicks] / device_ticks_per_ms(g->device);
   return MOSS_OK;
 }
 

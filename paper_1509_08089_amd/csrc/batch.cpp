@@ -268,7 +268,7 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
     for (uint64_t a = w.k0; a < w.k1; a += kBatchSortChunk) {
       const uint64_t n = std::min<uint64_t>(kBatchSortChunk, w.k1 - a);
       SortChunk c{w.sampler, w.seed, a, n, w.slot, window, 0, 0, view};
-      plain_launch_shape(w.g, w.sampler, n, &c.grid, &c.block);
+      grouped_launch_shape(w.g, w.sampler, n, &c.grid, &c.block);
       chunks.push_back(c);
       max_chunk = std::max(max_chunk, n);
     }
@@ -418,10 +418,12 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
     const int j = chains == 2 && load[1] < load[0] ? 1 : 0;
     load[j] += chunk_cost(c);
     const GroupChunk one{c.sampler, c.seed, c.a, c.n, sort_scratch_block[j], max_chunk};
-    e = launch_group_chunks(&one, 1, side_[j]);
+    e = launch_group_chunks(&one, 1, nullptr, side_[j]);
+    HitSink sink{};
+    sink.add = d_bins_ + (uint64_t)c.slot * 22;
     if (e == hipSuccess)
-      e = launch_sample_chunk(c.sampler, c.view, c.seed, c.a, c.n, sort_scratch_block[j], max_chunk, c.window,
-                              d_bins_ + (uint64_t)c.slot * 22, nullptr, c.grid, c.block, side_[j]);
+      e = launch_sample_chunk(c.sampler, c.view, c.seed, c.a, c.n, sort_scratch_block[j], max_chunk, c.window, sink,
+                              nullptr, c.grid, c.block, side_[j]);
   }
   for (int j = 0; j < side && e == hipSuccess; ++j) {
     e = hipEventRecord(ev_side_[j], side_[j]);

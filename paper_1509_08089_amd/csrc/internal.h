@@ -32,6 +32,7 @@ struct moss_graph {
 
   // per graph (mem_graph)
   uint64_t* small = nullptr;             // kWords words shared with the kernels
+  unsigned long long* hit_parts = nullptr;  // the sampling launches' partial counts, zero between calls
   uint64_t* items = nullptr;             // work items: rows cut into pieces of <= 256 entries
   uint64_t* item_sum = nullptr;          // n: piece counts, scanned into each row's item end (creation)
   uint64_t* guide_len = nullptr;         // n, row-guide lengths (creation only)
@@ -69,7 +70,7 @@ struct moss_graph {
   uint32_t built = 0;               // MOSS_TABLES_* bits
 
   uint64_t* h_stage = nullptr;      // pinned host staging, kWords words
-  hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  uint64_t host_seq = 0;            // calls that have had their counts put into h_stage
 
   std::atomic<int> busy{0};
   uint64_t csr_bytes = 0;
@@ -133,9 +134,10 @@ void free_graph_tables(moss_graph* g, uint32_t mask);
 // Device bytes that building `mask` would add to the graph.
 uint64_t table_bytes_needed(const moss_graph* g, uint32_t mask);
 
-// Launch shape of the plain sampling kernel for `nsamples` samples of graph g (the
-// process-wide tuning if set, else resident waves chosen by the graph's footprint).
-void plain_launch_shape(const moss_graph* g, int sampler, uint64_t nsamples, int* grid, int* block);
+// Launch shape of the sorted sampling kernel for `nsamples` samples of graph g (the
+// process-wide tuning if set, else resident waves by schedule and footprint).
+void grouped_launch_shape(const moss_graph* g, int sampler, uint64_t nsamples, int* grid, int* block);
+double device_ticks_per_ms(int device);
 int sampling_waves_per_cu(uint64_t footprint_bytes);
 uint64_t sampling_footprint(const moss_graph* g);
 bool grouped_schedule(const moss_graph* g, uint64_t nsamples);

@@ -58,7 +58,7 @@ constexpr int kWGuideLen = 5;  // entries of one row-guide array
 constexpr int kWUpper = 6;     // CSR entries (v, c) with c > v
 constexpr int kWMaxDeg = 7;    // largest degree
 constexpr int kWTotal = 8;     // totals of the Gamma, Gamma^(1), Gamma^(2), check-Gamma node weights
-constexpr int kWHits = 16;     // 2 x 22 hit counters of a plain estimate
+constexpr int kWBack = 16;     // words copied back after a table build
 constexpr int kWords = 64;
 
 // Rows with at least this many entries get a guide table for their weighted picks.
@@ -231,10 +231,45 @@ struct GuideSet {
 };
 hipError_t launch_guides(const GuideSet& set, int32_t n, int gbits, hipStream_t s);
 
-// Plain sampling launch: samples [k0, k1) of one sampler, hits[22] accumulated.  For
-// MOSS-4Min hits[7..9] also count the diamonds reached by 2, 4 and 6 ordered draws.
-hipError_t launch_sample(int sampler, const SamplerView& v, uint64_t seed, uint64_t k0, uint64_t k1,
-                         unsigned long long* hits, uint8_t* class_out, int grid, int block, hipStream_t s);
+// Where a sampling launch's counts go.  Its blocks add into `parts` (kHitPartsWords words,
+// zero between launches): kHitParts rows of 2 x 22 counts (`base`: the launch's first, 0 or
+// 22) and a ticket, then a row with the launch's ticket and start.  Of a call's launches the
+// last has `add` or `host` set: its last block sums and clears the rows and adds the sums to
+// add[2 x 22] (device), or stores them in host[2 x 22] (pinned), the device ticks since the
+// launch with `first` set in host[kHostTicks], and `seq` in host[kHostSeq] when all the
+// rest is there.  For MOSS-4Min the counts [7..9] are the diamonds reached by 2, 4 and 6
+// ordered draws.
+constexpr int kHitParts = 32;
+constexpr int kHitPartWords = 64;
+constexpr int kHitTicket = 44, kHitStart = 45;
+constexpr int kHitPartsWords = (kHitParts + 1) * kHitPartWords;
+constexpr int kHostTicks = 44, kHostSeq = 45;
+struct HitSink {
+  unsigned long long* parts;
+  unsigned long long* add;
+  unsigned long long* host;
+  uint64_t seq;
+  uint32_t base;
+  uint32_t first;
+};
+
+// Plain sampling launch: samples [k0, k1) of one sampler, or of MOSS-4 and MOSS-4Min or T-5
+// and Path-5 side by side, on at most most_blocks blocks.
+struct PlainLaunch {
+  int count;
+  int sampler[2];
+  SamplerView view[2];
+  uint64_t seed;
+  uint64_t k0[2], k1[2];
+  int most_blocks, block;
+};
+struct PlainJob {  // its kernel's argument
+  SamplerView view[2];
+  uint64_t seed;
+  uint64_t k0[2], k1[2];
+  uint32_t chunk[2], blocks[2];
+};
+hipError_t launch_sample(const PlainLaunch& l, const HitSink& sink, uint8_t* class_out, hipStream_t s);
 
 // The same samples drawn XCD-grouped, one chunk [a, a + n) at a time (n <= max_n <=
 // 2^26): the grouping passes (group of each sample, per-block group counts, their scan,
@@ -244,7 +279,7 @@ hipError_t launch_sample(int sampler, const SamplerView& v, uint64_t seed, uint6
 // events; a scratch block serves one chunk at a time.  block must be 64, 128, 192 or 256
 // threads; class_out (may be null) receives the chunk's classes at [0, n).
 // `window`: sorted entries a block takes at a time (sort_window of the bytes the
-// samples read at random).
+// samples read at random).  A sink without parts uses the scratch block's.
 int64_t grouped_scratch_bytes(uint64_t max_n);
 
 // The no-allocation calls' fixed scratch: a device array of kFixedScratchBytes that holds
@@ -262,9 +297,11 @@ struct GroupChunk {
   void* scratch;
   uint64_t max_n;
 };
-hipError_t launch_group_chunks(const GroupChunk* chunks, int count, hipStream_t s);  // one or two
+// One or two chunks; `start`: the sink parts that note the call's start, null if this is not
+// its first launch.
+hipError_t launch_group_chunks(const GroupChunk* chunks, int count, unsigned long long* start, hipStream_t s);
 hipError_t launch_sample_chunk(int sampler, const SamplerView& v, uint64_t seed, uint64_t a, uint64_t n,
-                               void* scratch, uint64_t max_n, uint32_t window, unsigned long long* hits,
+                               void* scratch, uint64_t max_n, uint32_t window, const HitSink& sink,
                                uint8_t* class_out, int grid, int block, hipStream_t s);
 
 hipError_t launch_sample_nodes(int sampler, const SamplerView& v, uint64_t seed, const uint64_t* index,

@@ -2390,6 +2390,72 @@ __device__ __forceinline__ void count_sample(uint32_t* bins, int c) {
   if (c >> 8) atomicAdd(&bins[c >> 8], 1u);
 }
 
+// A block's per-wave counters into the launch's sink (k_sample, k_sample_sorted).  Called by
+// every thread after a barrier; `base` is the sampler's first word in the counts.
+//
+// Blocks add into kHitParts rows of counts on lines of their own: added to one row, the
+// atomics of all blocks queue on its line, 13 ns a block (17 us at the end of a
+// 1280-block launch).  The last block of each row and then the last of the launch is
+// found by tickets; the last sums the rows, clears them for the next launch and hands the
+// counts over: to device counters, or to pinned host memory with the launch's device time
+// and then a sequence number, so that the host needs no copy, no events and no
+// synchronisation to have them (fill, two events, copy and synchronisation: about 14 us
+// of a call).  An estimate of 1e5 MOSS-4 samples on a small graph 39.0 -> 24.8 us; of 3e5
+// 5-node samples, with the two samplers in one launch, 83.6 -> 50.1 us; 1e7 MOSS-4 samples at
+// n = 1e5, m = 1e6, grouped, 416 -> 405 us.
+__device__ __forceinline__ void flush_hits(const uint32_t (&bins)[kMaxWaves][kBins + 2], const HitSink& k,
+                                           uint32_t base) {
+  if (threadIdx.x >= 64) return;
+  const int lane = threadIdx.x, nw = blockDim.x >> 6;
+  const uint32_t row = blockIdx.x % kHitParts;
+  unsigned long long* part = k.parts + row * kHitPartWords;
+  unsigned long long before = 0;
+  if (lane < kBins) {
+    uint64_t s = 0;
+    for (int w = 0; w < nw; ++w) s += bins[w][lane];
+    if (s) before = atomicAdd(&part[base + lane], (unsigned long long)s);
+  }
+  if (!k.add && !k.host) return;  // a later launch hands the counts over
+  // Only device-scope atomics touch the rows, so order is all that is needed and no fence (a
+  // fence a block writes back and drops its caches under the blocks still running: 5% of a
+  // launch): the counts' atomics have returned before the tickets go out.
+  asm volatile("" ::"v"((uint32_t)before) : "memory");
+  unsigned long long* all = k.parts + kHitParts * kHitPartWords;
+  uint32_t last = 0;
+  if (lane == 0) {
+    const uint32_t blocks = gridDim.x, mine = (blocks - row + kHitParts - 1) / kHitParts;
+    if (atomicAdd(&part[kHitTicket], 1ull) == mine - 1)
+      last = atomicAdd(&all[kHitTicket], 1ull) == min(blocks, (uint32_t)kHitParts) - 1;
+  }
+  if (!__builtin_amdgcn_readfirstlane(last)) return;
+  uint64_t sum = 0;
+  if (lane <= kHitTicket) {
+#pragma unroll 8
+    for (int i = 0; i < kHitParts; ++i)
+      sum += __hip_atomic_load(&k.parts[i * kHitPartWords + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll 8
+    for (int i = 0; i < kHitParts; ++i)
+      __hip_atomic_store(&k.parts[i * kHitPartWords + lane], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (lane == 0) __hip_atomic_store(&all[kHitTicket], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (k.add && lane < 2 * kBins && sum) atomicAdd(&k.add[lane], (unsigned long long)sum);
+  if (k.host) {
+    if (lane == kHostTicks)
+      sum = wall_clock64() - __hip_atomic_load(&all[kHitStart], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    static_assert(kHostTicks == 2 * kBins, "the ticks follow the counts");
+    if (lane <= kHostTicks) __hip_atomic_store(&k.host[lane], (unsigned long long)sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    if (lane == 0) __hip_atomic_store(&k.host[kHostSeq], (unsigned long long)k.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+// The first launch of a call notes when it starts (its block 0).
+__device__ __forceinline__ void stamp_start(unsigned long long* parts, uint32_t first) {
+  if (first && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+    __hip_atomic_store(&parts[kHitParts * kHitPartWords + kHitStart], (unsigned long long)wall_clock64(),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ---------------------------------------------------------------------------------
 // Lane order.  A sample's node v is monotone in its first random word W0 (the node draw
 // inverts the prefix of the node weights), so samples whose first words share their
@@ -2453,68 +2519,131 @@ __device__ void draw_lane_sorted(const SamplerView& a, const uint8_t* lut, uint6
   }
 }
 
-// Plain sampling: block b draws chunks b, b + grid, ... of `chunk` consecutive samples
-// (chunk <= kLaneChunk), each in lane order.
+// Samples [k0, k1) of one sampler by nb blocks: block b draws chunks b, b + nb, ... of
+// `chunk` consecutive samples (chunk <= kLaneChunk), each in lane order.
 template <int S>
-__global__ __launch_bounds__(256, kSampleWaves) void k_sample(SamplerView a, uint64_t seed, uint64_t k0, uint64_t k1,
-                                                uint32_t chunk, unsigned long long* __restrict__ hits,
-                                                uint8_t* __restrict__ class_out) {
-  __shared__ uint32_t bins[kMaxWaves][kBins + 2];
-  __shared__ uint8_t lut[64];
-  __shared__ LaneSort<kLaneChunk> ls;
-  const int tid = threadIdx.x, wave = tid >> 6, nw = blockDim.x >> 6;
-  for (int i = tid; i < nw * (kBins + 2); i += blockDim.x) bins[i / (kBins + 2)][i % (kBins + 2)] = 0;
+__device__ __forceinline__ void draw_chunks(const SamplerView& a, uint64_t seed, uint64_t k0, uint64_t k1,
+                                            uint32_t chunk, uint32_t b, uint32_t nb, LaneSort<kLaneChunk>& ls,
+                                            uint8_t* lut, uint32_t* bins, uint8_t* __restrict__ class_out) {
   load_lut<S>(lut);
   __syncthreads();
-  const uint64_t stride = (uint64_t)gridDim.x * chunk;
-  for (uint64_t s0 = k0 + (uint64_t)blockIdx.x * chunk; s0 < k1; s0 += stride) {
+  const uint64_t stride = (uint64_t)nb * chunk;
+  for (uint64_t s0 = k0 + (uint64_t)b * chunk; s0 < k1; s0 += stride) {
     const uint32_t n = (uint32_t)min((uint64_t)chunk, k1 - s0);
     lane_sort<S>(ls, seed, [&](uint32_t j) { return s0 + j; }, n, 56);
-    for (uint32_t j = tid; j < n; j += blockDim.x) {
+    for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) {
       const uint64_t k = s0 + ls.order[j];
       const int c = draw<S>(a, lut, seed, k, nullptr);
-      count_sample(bins[wave], c);
+      count_sample(bins, c);
       if (class_out) class_out[k - k0] = (uint8_t)c;
     }
     __syncthreads();  // the next chunk reuses ls
   }
-  if (tid < kBins) {
-    uint64_t s = 0;
-    for (int w = 0; w < nw; ++w) s += bins[w][tid];
-    if (s) atomicAdd(&hits[tid], (unsigned long long)s);
-  }
 }
 
-hipError_t launch_sample(int sampler, const SamplerView& v, uint64_t seed, uint64_t k0, uint64_t k1,
-                         unsigned long long* hits, uint8_t* class_out, int grid, int block, hipStream_t s) {
-  if (grid < 1 || block < 64 || block > 256 || block % 64) return hipErrorInvalidValue;
-  // a chunk per block and round that spreads the samples over the whole grid, between
-  // one sample per thread and kLaneChunk; per-wave LDS counters are 32-bit, so each
-  // launch stays below 2^31 samples per wave
-  const uint64_t per_round = (k1 - k0 + (uint64_t)grid - 1) / (uint64_t)grid;
-  const uint32_t chunk = (uint32_t)std::min<uint64_t>(kLaneChunk, std::max<uint64_t>((uint64_t)block, per_round));
-  const uint64_t max_chunk = (uint64_t)grid * (uint64_t)block * (1ull << 24);
-  for (uint64_t a = k0; a < k1;) {
-    const uint64_t b = k1 - a > max_chunk ? a + max_chunk : k1;
-    uint8_t* co = class_out ? class_out + (a - k0) : nullptr;
-    switch (sampler) {
-      case kMoss4:
-        hipLaunchKernelGGL(k_sample<kMoss4>, dim3(grid), dim3(block), 0, s, v, seed, a, b, chunk, hits, co);
-        break;
-      case kMoss4Min:
-        hipLaunchKernelGGL(k_sample<kMoss4Min>, dim3(grid), dim3(block), 0, s, v, seed, a, b, chunk, hits, co);
-        break;
-      case kT5: hipLaunchKernelGGL(k_sample<kT5>, dim3(grid), dim3(block), 0, s, v, seed, a, b, chunk, hits, co); break;
-      case kPath5:
-        hipLaunchKernelGGL(k_sample<kPath5>, dim3(grid), dim3(block), 0, s, v, seed, a, b, chunk, hits, co);
-        break;
-      default: return hipErrorInvalidValue;
+// Plain sampling of one sampler, or (S1 != 0) of an estimate's two in one launch: the first
+// blocks[0] blocks draw the first sampler's samples, the others the second's, so that two
+// samplers of a small estimate, neither of which fills the chip, run side by side.
+template <int S0, int S1>
+__global__ __launch_bounds__(256, kSampleWaves) void k_sample(PlainJob p, HitSink sink, uint8_t* __restrict__ class_out) {
+  __shared__ uint32_t bins[kMaxWaves][kBins + 2];
+  __shared__ uint8_t lut[64];
+  __shared__ LaneSort<kLaneChunk> ls;
+  const int tid = threadIdx.x, wave = tid >> 6, nw = blockDim.x >> 6;
+  stamp_start(sink.parts, sink.first);
+  for (int i = tid; i < nw * (kBins + 2); i += blockDim.x) bins[i / (kBins + 2)][i % (kBins + 2)] = 0;
+  const bool second = S1 != 0 && blockIdx.x >= p.blocks[0];
+  if (!second)
+    draw_chunks<S0>(p.view[0], p.seed, p.k0[0], p.k1[0], p.chunk[0], blockIdx.x, p.blocks[0], ls, lut, bins[wave],
+                    class_out);
+  else if constexpr (S1 != 0)
+    draw_chunks<S1>(p.view[1], p.seed, p.k0[1], p.k1[1], p.chunk[1], blockIdx.x - p.blocks[0], p.blocks[1], ls, lut,
+                    bins[wave], class_out);
+  __syncthreads();
+  flush_hits(bins, sink, second ? kBins : sink.base);
+}
+
+namespace {
+
+template <typename F>
+auto with_plain_kernel(int s0, int s1, F f) {
+  if (s1 == 0) {
+    switch (s0) {
+      case kMoss4: return f(k_sample<kMoss4, 0>);
+      case kMoss4Min: return f(k_sample<kMoss4Min, 0>);
+      case kT5: return f(k_sample<kT5, 0>);
+      default: return f(k_sample<kPath5, 0>);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    a = b;
   }
-  return hipSuccess;
+  return s0 == kMoss4 ? f(k_sample<kMoss4, kMoss4Min>) : f(k_sample<kT5, kPath5>);
+}
+
+// What a sample costs, about: T-5 / Path-5 and MOSS-4 / MOSS-4Min measured 1 / 1.35 to 1.5.
+uint64_t sample_cost(int sampler) { return sampler == kMoss4 || sampler == kT5 ? 2 : 3; }
+
+}  // namespace
+
+hipError_t launch_sample(const PlainLaunch& l, const HitSink& sink, uint8_t* class_out, hipStream_t s) {
+  const bool two = l.count == 2;
+  if (l.count < 1 || l.count > 2 || l.most_blocks < l.count || l.block < 64 || l.block > 256 || l.block % 64 ||
+      (two && !(l.sampler[0] == kMoss4 && l.sampler[1] == kMoss4Min) &&
+       !(l.sampler[0] == kT5 && l.sampler[1] == kPath5)))
+    return hipErrorInvalidValue;
+  for (int i = 0; i < l.count; ++i)
+    if (l.k1[i] <= l.k0[i] || (l.sampler[i] != kMoss4 && l.sampler[i] != kMoss4Min && l.sampler[i] != kT5 &&
+                               l.sampler[i] != kPath5))
+      return hipErrorInvalidValue;
+  // One sample a thread while all blocks are resident, else the blocks split by cost
+  uint64_t want[2] = {0, 0}, blocks[2] = {0, 0};
+  const uint64_t most = (uint64_t)l.most_blocks, block = (uint64_t)l.block;
+  for (int i = 0; i < l.count; ++i) want[i] = (l.k1[i] - l.k0[i] + block - 1) / block;
+  if (!two) {
+    blocks[0] = std::min(want[0], most);
+  } else if (want[0] + want[1] <= most) {
+    blocks[0] = want[0];
+    blocks[1] = want[1];
+  } else {
+    const double c0 = (double)want[0] * (double)sample_cost(l.sampler[0]);
+    const double c1 = (double)want[1] * (double)sample_cost(l.sampler[1]);
+    blocks[0] = std::min(std::max<uint64_t>(1, (uint64_t)((double)most * (c0 / (c0 + c1)))), most - 1);
+    blocks[1] = most - blocks[0];
+  }
+  PlainJob p{};
+  p.seed = l.seed;
+  uint64_t at[2] = {0, 0};
+  for (int i = 0; i < l.count; ++i) {
+    // a chunk per block and round that spreads the samples over the sampler's blocks,
+    // between one sample per thread and kLaneChunk
+    const uint64_t per_round = (l.k1[i] - l.k0[i] + blocks[i] - 1) / blocks[i];
+    p.view[i] = l.view[i];
+    p.blocks[i] = (uint32_t)blocks[i];
+    p.chunk[i] = (uint32_t)std::min<uint64_t>(kLaneChunk, std::max<uint64_t>(block, per_round));
+    at[i] = l.k0[i];
+  }
+  // per-wave LDS counters are 32-bit, so a launch stays below 2^31 samples per wave
+  HitSink k = sink;
+  for (;;) {
+    bool more = false;
+    for (int i = 0; i < l.count; ++i) {
+      const uint64_t part = blocks[i] * block * (1ull << 24);
+      p.k0[i] = at[i];
+      p.k1[i] = l.k1[i] - at[i] > part ? at[i] + part : l.k1[i];
+      more |= p.k1[i] < l.k1[i];
+    }
+    if (more) k.add = k.host = nullptr;  // the last launch hands the counts over
+    else {
+      k.add = sink.add;
+      k.host = sink.host;
+    }
+    uint8_t* out = class_out ? class_out + (p.k0[0] - l.k0[0]) : nullptr;
+    with_plain_kernel(l.sampler[0], two ? l.sampler[1] : 0, [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks[0] + blocks[1])), dim3(l.block), 0, s, p, k, out);
+    });
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !more) return e;
+    for (int i = 0; i < l.count; ++i) at[i] = p.k1[i];
+    k.first = 0;
+  }
 }
 
 // ---------------------------------------------------------------------------------
@@ -2597,6 +2726,7 @@ struct SortScratch {
   uint32_t* gtot;     // kSortGroups: samples per group
   uint32_t* gstart;   // kSortGroups + 1: start of each group in the sorted order (the last is n)
   uint32_t* cursors;  // kXcds window cursors, kCursorStride apart
+  unsigned long long* parts;  // partial counts of the chunk's sampling launch (kHitPartsWords)
   uint32_t nblk;      // blocks (rows) of this chunk
 };
 
@@ -2607,6 +2737,7 @@ struct SortJob {
 };
 struct SortJobs {
   SortJob job[2];
+  unsigned long long* start;  // the parts that note the call's start (null: not the call's first launch)
 };
 
 __device__ __forceinline__ uint4* quad_at(uint32_t* table, uint32_t row, uint32_t q) {
@@ -2638,6 +2769,7 @@ static SortScratch sort_scratch(void* base, uint64_t max_n) {
   t.gtot = reinterpret_cast<uint32_t*>(take((size_t)kSortGroups * 4));
   t.gstart = reinterpret_cast<uint32_t*>(take((size_t)(kSortGroups + 1) * 4));
   t.cursors = reinterpret_cast<uint32_t*>(take(kXcds * kCursorStride * 4));
+  t.parts = reinterpret_cast<unsigned long long*>(take(kHitPartsWords * 8));
   return t;
 }
 
@@ -2646,7 +2778,7 @@ constexpr uint64_t scratch_bytes_for(uint64_t max_n) {
   auto r = [](uint64_t b) { return (b + 255) / 256 * 256; };
   return r(max_n * 2) + r(max_n * 4) + 2 * r(kSortGroups * nblk * 4) +
          r(kSortGroups * 4) + r((kSortGroups + 1) * 4) +
-         r(kXcds * kCursorStride * 4) + 256;
+         r(kXcds * kCursorStride * 4) + r(kHitPartsWords * 8) + 256;
 }
 
 int64_t grouped_scratch_bytes(uint64_t max_n) { return (int64_t)scratch_bytes_for(max_n); }
@@ -2696,7 +2828,11 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_count(SortJobs jobs) {
   const SortJob& job = jobs.job[blockIdx.y];
   const SortScratch& t = job.t;
   if (blockIdx.x >= t.nblk) return;  // whole blocks: the other job has more rows
-  if (blockIdx.x == 0 && threadIdx.x < kXcds) t.cursors[threadIdx.x * kCursorStride] = 0;
+  stamp_start(jobs.start, jobs.start != nullptr);
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < kXcds) t.cursors[threadIdx.x * kCursorStride] = 0;
+    for (int i = threadIdx.x; i < kHitPartsWords; i += kSortThreads) t.parts[i] = 0;
+  }
   hist[threadIdx.x] = 0;
   __syncthreads();
   const uint64_t lo = (uint64_t)blockIdx.x * kSortSpan;
@@ -2813,8 +2949,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(SortJobs jobs) {
 
 template <int S>
 __global__ __launch_bounds__(256, kSampleWaves) void k_sample_sorted(SamplerView a, uint64_t seed, uint64_t k0, uint64_t n,
-                                                       SortScratch t, uint32_t window,
-                                                       unsigned long long* __restrict__ hits,
+                                                       SortScratch t, uint32_t window, HitSink sink,
                                                        uint8_t* __restrict__ class_out) {
   __shared__ uint32_t bins[kMaxWaves][kBins + 2];
   __shared__ uint8_t lut[64];
@@ -2871,16 +3006,13 @@ __global__ __launch_bounds__(256, kSampleWaves) void k_sample_sorted(SamplerView
     }
   }
   __syncthreads();
-  if (tid < kBins) {
-    uint64_t s = 0;
-    for (int w = 0; w < nw; ++w) s += bins[w][tid];
-    if (s) atomicAdd(&hits[tid], (unsigned long long)s);
-  }
+  flush_hits(bins, sink, sink.base);
 }
 
-hipError_t launch_group_chunks(const GroupChunk* chunks, int count, hipStream_t s) {
+hipError_t launch_group_chunks(const GroupChunk* chunks, int count, unsigned long long* start, hipStream_t s) {
   if (count < 1 || count > 2) return hipErrorInvalidValue;
   SortJobs jobs{};
+  jobs.start = start;
   uint32_t most = 0;
   for (int i = 0; i < count; ++i) {
     const GroupChunk& c = chunks[i];
@@ -2901,37 +3033,30 @@ hipError_t launch_group_chunks(const GroupChunk* chunks, int count, hipStream_t 
 }
 
 hipError_t launch_sample_chunk(int sampler, const SamplerView& v, uint64_t seed, uint64_t a, uint64_t n,
-                               void* scratch, uint64_t max_n, uint32_t window, unsigned long long* hits,
+                               void* scratch, uint64_t max_n, uint32_t window, const HitSink& sink,
                                uint8_t* class_out, int grid, int block, hipStream_t s) {
   if (block != 64 * (block / 64) || block > 256 || block < 64 || n == 0 || n > max_n ||
       max_n > (1ull << kOrderBits) || window == 0 || window > (uint32_t)kMaxWindow)
     return hipErrorInvalidValue;
   SortScratch tc = sort_scratch(scratch, max_n);
   tc.nblk = sort_blocks(n);
+  HitSink k = sink;
+  if (!k.parts) k.parts = tc.parts;  // cleared by the grouping pass
   // no more blocks than windows (each block visits every cursor once at least), a
   // multiple of the XCD count so that every XCD gets its share of blocks
   const uint64_t wins = (n + window - 1) / window;
   const int g = (int)std::min<uint64_t>((uint64_t)grid, std::max<uint64_t>(kXcds, (wins + kXcds - 1) / kXcds * kXcds));
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g), dim3(block), 0, s, v, seed, a, n, tc, window, k, class_out);
+    return hipGetLastError();
+  };
   switch (sampler) {
-    case kMoss4:
-      hipLaunchKernelGGL(k_sample_sorted<kMoss4>, dim3(g), dim3(block), 0, s, v, seed, a, n, tc, window, hits,
-                         class_out);
-      break;
-    case kMoss4Min:
-      hipLaunchKernelGGL(k_sample_sorted<kMoss4Min>, dim3(g), dim3(block), 0, s, v, seed, a, n, tc, window, hits,
-                         class_out);
-      break;
-    case kT5:
-      hipLaunchKernelGGL(k_sample_sorted<kT5>, dim3(g), dim3(block), 0, s, v, seed, a, n, tc, window, hits,
-                         class_out);
-      break;
-    case kPath5:
-      hipLaunchKernelGGL(k_sample_sorted<kPath5>, dim3(g), dim3(block), 0, s, v, seed, a, n, tc, window, hits,
-                         class_out);
-      break;
+    case kMoss4: return go(k_sample_sorted<kMoss4>);
+    case kMoss4Min: return go(k_sample_sorted<kMoss4Min>);
+    case kT5: return go(k_sample_sorted<kT5>);
+    case kPath5: return go(k_sample_sorted<kPath5>);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 template <int S>
@@ -3031,14 +3156,11 @@ hipError_t launch_batch(const SamplerView* views, const BatchItem* items, uint32
 
 int sample_kernel_blocks_per_cu(int sampler, int block) {
   int nb = 0;
-  hipError_t e = hipSuccess;
-  switch (sampler) {
-    case kMoss4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sample<kMoss4>, block, 0); break;
-    case kMoss4Min: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sample<kMoss4Min>, block, 0); break;
-    case kT5: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sample<kT5>, block, 0); break;
-    case kPath5: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_sample<kPath5>, block, 0); break;
-    default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_batch, block, 0); break;
-  }
+  const hipError_t e =
+      sampler == 0 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_batch, block, 0)
+                   : with_plain_kernel(sampler, 0, [&](auto kernel) {
+                       return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, block, 0);
+                     });
   return e == hipSuccess ? nb : 0;
 }
 
