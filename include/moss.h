@@ -319,7 +319,7 @@ moss_status moss_estimate_batch(const moss_request *reqs, int32_t n, moss_result
    the sampling kernels; schedule: how a plain estimate spreads its samples
    (MOSS_SCHEDULE_*); group_min_samples_log2 / group_min_footprint_mb: a batched or
    served item runs as an XCD-grouped launch of its own (instead of in the persistent
-   kernel) when it has at least 2^group_min_samples_log2 samples (default 2^20) on a
+   kernel) when it has at least 2^group_min_samples_log2 samples (default 2^18) on a
    graph whose sampled bytes reach group_min_footprint_mb MB (default 32).  No knob
    changes any result. */
 enum {

@@ -117,9 +117,12 @@ SamplerView sampler_view(const moss_graph* g, int sampler) {
 // Resident waves per CU for the sampling kernels, by the bytes a graph's samples read
 // at random (CSR and tables).  Measured on MI355X: a graph whose tables fit the 256 MB
 // MALL samples fastest with about 20 waves per CU; one far larger than the MALL with
-// 8 (more waves in flight then only add queueing and translation misses).
+// 8 (more waves in flight then only add queueing and translation misses).  Tables that
+// fit one XCD's 4 MB L2 take 28 (m = 1e4, 4e6 MOSS-4 samples: 105 us at 20, 96 at 28; at
+// m = 1e5, 11 MB, 157 and 159).
 int sampling_waves_per_cu(uint64_t footprint_bytes) {
   const uint64_t MB = 1ull << 20;
+  if (footprint_bytes <= 4 * MB) return 28;
   if (footprint_bytes <= 128 * MB) return 20;
   if (footprint_bytes <= 256 * MB) return 16;
   if (footprint_bytes <= 384 * MB) return 12;

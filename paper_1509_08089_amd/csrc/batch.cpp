@@ -20,10 +20,19 @@ std::map<int, std::unique_ptr<BatchRunner>> g_runners;
 
 constexpr uint32_t kDefaultTile = 4096;
 
-// Batched items drawn by grouped launches of their own: at least 2^20 samples on a graph
+// Resident waves per CU of the persistent kernel.  Its tiles are drawn in lane order, so
+// more waves hide latency on large graphs too: 12 / 16 / 20 / 24 / 28 waves on 256
+// requests over 32 graphs (m to 5e6) 19.4 / 18.5 / 18.5 / 18.5 / 18.6 ms, on 64 requests over
+// 8 graphs (m to 3e5) 1.78 / 1.64 / 1.58 / 1.57 / 1.56 ms, on 40 over 6 (m from 1e6 to
+// 8e6) 8.67 / 8.28 / 8.50 / 8.55 / 8.68 ms.
+constexpr int kBatchWaves = 24;
+
+// Batched items drawn by grouped launches of their own: at least 2^18 samples on a graph
 // whose sampled bytes are past 32 MB (the tuning's schedule overrides: PLAIN never, XCD
-// always).
-constexpr uint64_t kBatchSortMinSamples = 1ull << 20;
+// always).  At 24 waves, from 2^17 / 2^18 / 2^19 / 2^20 samples: 18.24 / 18.30 / 18.34 /
+// 18.48 ms on the first of those batches, 8.03 / 8.04 / 8.18 / 8.55 ms on the last; from 16
+// or 64 MB on no faster.
+constexpr uint64_t kBatchSortMinSamples = 1ull << 18;
 constexpr uint64_t kBatchSortMinFootprint = 32ull << 20;
 constexpr uint64_t kBatchSortChunk = 1ull << 25;
 
@@ -233,12 +242,7 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
   uint32_t T = tile_samples ? tile_samples : (tune.tile_samples ? tune.tile_samples : kDefaultTile);
   const int block = tune.threads_per_block ? (int)tune.threads_per_block : 256;
   int bpc = blocks_per_cu ? (int)blocks_per_cu : (int)tune.blocks_per_cu;
-  if (bpc == 0) {  // by the largest graph of the batch (its tiles run together)
-    uint64_t most = 0;
-    for (const WorkItem& w : work) most = std::max(most, sampling_footprint(w.g));
-    const int cap = std::max(1, std::min(8, sample_kernel_blocks_per_cu(0, block)));
-    bpc = std::max(1, std::min(cap, sampling_waves_per_cu(most) / (block / 64)));
-  }
+  if (bpc == 0) bpc = std::max(1, std::min(kBatchWaves / (block / 64), sample_kernel_blocks_per_cu(0, block)));
   const int grid = device_cus(device_) * bpc;
 
   // views: one per distinct (graph, sampler)

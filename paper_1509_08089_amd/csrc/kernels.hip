@@ -2520,7 +2520,10 @@ __device__ void draw_lane_sorted(const SamplerView& a, const uint8_t* lut, uint6
 }
 
 // Samples [k0, k1) of one sampler by nb blocks: block b draws chunks b, b + nb, ... of
-// `chunk` consecutive samples (chunk <= kLaneChunk), each in lane order.
+// `chunk` consecutive samples (chunk <= kLaneChunk), each in lane order.  A chunk of one
+// sample a thread goes in index order: the order of 64 among 256 samples gains less than
+// its Philox block and four barriers cost (1e5 samples: 21 -> 20 us an estimate at
+// m = 1e4, 31 -> 30 at m = 3e6); from 1e6 samples on it is worth 10% (m = 1e4) to 50%.
 template <int S>
 __device__ __forceinline__ void draw_chunks(const SamplerView& a, uint64_t seed, uint64_t k0, uint64_t k1,
                                             uint32_t chunk, uint32_t b, uint32_t nb, LaneSort<kLaneChunk>& ls,
@@ -2530,9 +2533,10 @@ __device__ __forceinline__ void draw_chunks(const SamplerView& a, uint64_t seed,
   const uint64_t stride = (uint64_t)nb * chunk;
   for (uint64_t s0 = k0 + (uint64_t)b * chunk; s0 < k1; s0 += stride) {
     const uint32_t n = (uint32_t)min((uint64_t)chunk, k1 - s0);
-    lane_sort<S>(ls, seed, [&](uint32_t j) { return s0 + j; }, n, 56);
+    const bool sorted = chunk > blockDim.x;
+    if (sorted) lane_sort<S>(ls, seed, [&](uint32_t j) { return s0 + j; }, n, 56);
     for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) {
-      const uint64_t k = s0 + ls.order[j];
+      const uint64_t k = s0 + (sorted ? ls.order[j] : j);
       const int c = draw<S>(a, lut, seed, k, nullptr);
       count_sample(bins, c);
       if (class_out) class_out[k - k0] = (uint8_t)c;
@@ -2612,12 +2616,14 @@ hipError_t launch_sample(const PlainLaunch& l, const HitSink& sink, uint8_t* cla
   p.seed = l.seed;
   uint64_t at[2] = {0, 0};
   for (int i = 0; i < l.count; ++i) {
-    // a chunk per block and round that spreads the samples over the sampler's blocks,
-    // between one sample per thread and kLaneChunk
-    const uint64_t per_round = (l.k1[i] - l.k0[i] + blocks[i] - 1) / blocks[i];
+    // chunks that spread the samples evenly over the sampler's blocks in as few rounds as
+    // kLaneChunk allows, of at least one sample per thread (full chunks leave the last round
+    // to a few blocks: 8e6 5-node samples at m = 1e5 517 us against 477)
+    const uint64_t per_block = (l.k1[i] - l.k0[i] + blocks[i] - 1) / blocks[i];
+    const uint64_t rounds = (per_block + kLaneChunk - 1) / kLaneChunk;
     p.view[i] = l.view[i];
     p.blocks[i] = (uint32_t)blocks[i];
-    p.chunk[i] = (uint32_t)std::min<uint64_t>(kLaneChunk, std::max<uint64_t>(block, per_round));
+    p.chunk[i] = (uint32_t)std::max<uint64_t>(block, (per_block + rounds - 1) / rounds);
     at[i] = l.k0[i];
   }
   // per-wave LDS counters are 32-bit, so a launch stays below 2^31 samples per wave
