@@ -2,7 +2,7 @@
 
 Headline (`value`): the batched configuration C4.  256 estimation requests (k in {4, 5},
 budgets log-uniform in [1e4, 1e7], 3.46e8 samples in all) over 32 resident Chung-Lu
-graphs (m log-uniform in [1e3, 5e6]) run as one batched launch: a hipGraph-replayed
+graphs (m log-uniform in [1e3, 5e6]) run as one batched launch: a
 persistent kernel over a tile list, plus grouped launches for the large items on the
 larger graphs, with the tile size and occupancy picked by the library's autotuner.
 A step is one such launch over all 256 requests (the graphs' tables are built before the
@@ -66,7 +66,7 @@ WORKLOAD_TEXT = {
     "C2": "plain 4-node MOSS-4, Chung-Lu n=1e5 m=1e6 beta=2.2 dmax=3e3, 1e7 samples, seed 1",
     "C3": "plain 5-node MOSS-5 (T-5 + Path-5), Chung-Lu n=1e6 m=1e7 beta=2.1 dmax=2e4, 1e8 samples, seed 1",
     "C4": "batched: 256 requests (k in {4,5}, budgets log-uniform 1e4..1e7) over 32 resident Chung-Lu graphs "
-          "(m log-uniform 1e3..5e6), one persistent hipGraph launch with autotuned tiles",
+          "(m log-uniform 1e3..5e6), one persistent launch with autotuned tiles",
     "C5": "serving: Poisson 500 req/s over 64 resident Chung-Lu graphs (m 1e3..3.5e7, largest n=4e6 beta=2.0), "
           "k in {4,5}, budgets log-uniform 1e4..1e8, memory-based admission",
 }
@@ -75,7 +75,7 @@ WORKLOAD_TEXT = {
 # passes and sampling kernels; the batched launch's clear, persistent kernel and grouped
 # launches)
 LAUNCH_KERNELS = ("k_sort_count", "k_sort_scan", "k_sort_scatter",
-                  "k_sample_sorted", "k_sample<", "k_batch", "k_fill_u64", "k_fill_u32")
+                  "k_sample_sorted", "k_sample<", "k_batch")
 
 
 def log(*a):

@@ -151,8 +151,7 @@ typedef struct {
   uint64_t lambda;         /* k=4: Lambda_3; k=5: Lambda_4 */
   double estimate[21];     /* estimate[i-1] of n_i (k=4, i <= 6) or eta_i (k=5) */
   double variance[21];     /* Theorem 3 / Theorem 10 evaluated at the estimates */
-  double device_ms;        /* device time of the sampling kernels, by the device's clock
-                              (batched: HIP events around the batch) */
+  double device_ms;        /* device time of the sampling kernels, by the device's clock */
 } moss_result;
 
 /* ---- errors ---------------------------------------------------------------------- */
@@ -296,7 +295,7 @@ moss_status moss_estimate_to_precision(moss_graph *g, int32_t k, double eps, dou
 moss_status moss_concentrations(const moss_result *r, double omega[21]);
 
 /* ---- batching: many requests in one persistent launch --------------------------------
- * One persistent kernel (replayed from a captured hipGraph) takes the requests' sample
+ * One persistent kernel takes the requests' sample
  * ranges as a list of items in graph-major order, cuts them into tiles of consecutive
  * sample indices as its workgroups ask for work, draws each tile's samples in the order
  * of their first random word, and keeps per-request hit counts; items with many samples

@@ -1,5 +1,5 @@
 // Batched estimation: many (graph, k, budget, seed) requests drained by one
-// persistent kernel launch, replayed from a captured hipGraph.
+// persistent kernel launch.
 #include "batch.h"
 
 #include <algorithm>
@@ -97,27 +97,17 @@ BatchRunner::~BatchRunner() {
 void BatchRunner::release() {
   DeviceScope scope(device_);
   if (stream_) (void)hipStreamSynchronize(stream_);
-  if (exec_) (void)hipGraphExecDestroy(exec_);
-  if (graph_) (void)hipGraphDestroy(graph_);
-  exec_ = nullptr;
-  graph_ = nullptr;
-  graph_grid_ = graph_block_ = 0;
-  if (d_views_) (void)hipFree(d_views_);
-  if (d_items_) (void)hipFree(d_items_);
-  if (d_ctl_) (void)hipFree(d_ctl_);
+  if (d_in_) (void)hipFree(d_in_);
   if (d_bins_) (void)hipFree(d_bins_);
-  d_views_ = nullptr;
-  d_items_ = nullptr;
-  d_ctl_ = nullptr;
+  if (d_end_) (void)hipFree(d_end_);
+  d_in_ = nullptr;
   d_bins_ = nullptr;
-  cap_views_ = cap_items_ = cap_slots_ = 0;
+  d_end_ = nullptr;
+  cap_in_ = cap_slots_ = 0;
   if (h_in_) (void)hipHostFree(h_in_);
   if (h_bins_) (void)hipHostFree(h_bins_);
   h_in_ = nullptr;
   h_bins_ = nullptr;
-  cap_in_ = 0;
-  if (ev0_) (void)hipEventDestroy(ev0_);
-  if (ev1_) (void)hipEventDestroy(ev1_);
   if (ev_wait_) (void)hipEventDestroy(ev_wait_);
   if (ev_clear_) (void)hipEventDestroy(ev_clear_);
   for (int j = 0; j < 2; ++j) {
@@ -129,100 +119,39 @@ void BatchRunner::release() {
     }
     side_[j] = nullptr;
   }
-  ev0_ = ev1_ = ev_wait_ = ev_clear_ = nullptr;
+  ev_wait_ = ev_clear_ = nullptr;
   if (stream_) (void)hipStreamDestroy(stream_);
   stream_ = nullptr;
 }
 
-moss_status BatchRunner::reserve(size_t views, size_t items, size_t slots) {
-  bool changed = false;
-  auto grow = [&](size_t need, size_t& cap, auto** ptr, size_t elem) -> moss_status {
-    if (need <= cap) return MOSS_OK;
-    size_t c = std::max<size_t>(need, cap * 2);
-    if (*ptr) (void)hipFree((void*)*ptr);
-    *ptr = nullptr;
-    if (hipMalloc((void**)ptr, c * elem) != hipSuccess) {
-      *ptr = nullptr;
-      cap = 0;
-      return MOSS_E_NOMEM;
-    }
-    cap = c;
-    changed = true;
-    return MOSS_OK;
+// Room for `bytes` of views, items and control words and for `slots` histogram slots, on
+// the device and in pinned host memory.
+moss_status BatchRunner::reserve(size_t bytes, size_t slots) {
+  auto device = [](auto** p, size_t size) {
+    if (*p) (void)hipFree((void*)*p);
+    *p = nullptr;
+    return hipMalloc((void**)p, size) == hipSuccess || (*p = nullptr);
   };
-  moss_status st = grow(std::max<size_t>(views, 64), cap_views_, &d_views_, sizeof(SamplerView));
-  if (st == MOSS_OK) st = grow(std::max<size_t>(items, 512), cap_items_, &d_items_, sizeof(BatchItem));
-  if (st == MOSS_OK) {
-    const size_t old = cap_slots_;
-    st = grow(std::max<size_t>(slots, 512), cap_slots_, &d_bins_, 22 * sizeof(unsigned long long));
-    if (st == MOSS_OK && cap_slots_ != old) {
-      if (h_bins_) (void)hipHostFree(h_bins_);
-      h_bins_ = nullptr;
-      if (hipHostMalloc((void**)&h_bins_, cap_slots_ * 22 * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess) {
-        h_bins_ = nullptr;
-        return MOSS_E_NOMEM;
-      }
-    }
+  auto host = [](auto** p, size_t size) {
+    if (*p) (void)hipHostFree((void*)*p);
+    *p = nullptr;
+    return hipHostMalloc((void**)p, size, hipHostMallocDefault) == hipSuccess || (*p = nullptr);
+  };
+  if (!d_end_ && !device(&d_end_, 2 * sizeof(unsigned long long))) return MOSS_E_NOMEM;
+  if (bytes > cap_in_) {
+    const size_t c = std::max<size_t>({bytes, 2 * cap_in_, 64 << 10});
+    cap_in_ = 0;
+    if (!device(&d_in_, c) || !host(&h_in_, c)) return MOSS_E_NOMEM;
+    cap_in_ = c;
   }
-  if (st != MOSS_OK) return st;
-  if (!d_ctl_) {
-    if (hipMalloc((void**)&d_ctl_, 4 * sizeof(uint32_t)) != hipSuccess) {
-      d_ctl_ = nullptr;
+  if (slots > cap_slots_) {
+    const size_t c = std::max<size_t>({slots, 2 * cap_slots_, 512});
+    cap_slots_ = 0;
+    if (!device(&d_bins_, c * 22 * sizeof(unsigned long long)) ||
+        !host(&h_bins_, (kBatchHostWords + c * 22) * sizeof(uint64_t)))
       return MOSS_E_NOMEM;
-    }
-    changed = true;
+    cap_slots_ = c;
   }
-  const size_t in_bytes = cap_views_ * sizeof(SamplerView) + cap_items_ * sizeof(BatchItem) + 64;
-  if (in_bytes > cap_in_) {
-    if (h_in_) (void)hipHostFree(h_in_);
-    h_in_ = nullptr;
-    if (hipHostMalloc((void**)&h_in_, in_bytes, hipHostMallocDefault) != hipSuccess) {
-      h_in_ = nullptr;
-      cap_in_ = 0;
-      return MOSS_E_NOMEM;
-    }
-    cap_in_ = in_bytes;
-  }
-  if (changed && exec_) {
-    (void)hipGraphExecDestroy(exec_);
-    (void)hipGraphDestroy(graph_);
-    exec_ = nullptr;
-    graph_ = nullptr;
-  }
-  return MOSS_OK;
-}
-
-// Captures: clear the tile counter (a fill kernel), then the persistent kernel.  Its
-// arguments are the fixed buffers above, so one capture serves every batch until a
-// buffer is reallocated or the launch shape changes.  (The histogram slots are cleared
-// before the graph, so that the grouped launches on the side stream can start with it.)
-moss_status BatchRunner::capture(int grid, int block) {
-  if (exec_ && grid == graph_grid_ && block == graph_block_) return MOSS_OK;
-  if (exec_) {
-    (void)hipGraphExecDestroy(exec_);
-    (void)hipGraphDestroy(graph_);
-    exec_ = nullptr;
-    graph_ = nullptr;
-  }
-  hipError_t e = hipStreamBeginCapture(stream_, hipStreamCaptureModeThreadLocal);
-  if (e != hipSuccess) return status_of(e);
-  hipError_t e1 = launch_fill_u32(d_ctl_ + kCtlCounter, 0, 1, stream_);
-  if (e1 == hipSuccess) e1 = launch_batch(d_views_, d_items_, d_ctl_, d_bins_, grid, block, stream_);
-  hipGraph_t g = nullptr;
-  e = hipStreamEndCapture(stream_, &g);
-  if (e1 != hipSuccess || e != hipSuccess) {
-    if (g) (void)hipGraphDestroy(g);
-    return status_of(e1 != hipSuccess ? e1 : e);
-  }
-  e = hipGraphInstantiate(&exec_, g, nullptr, nullptr, 0);
-  if (e != hipSuccess) {
-    (void)hipGraphDestroy(g);
-    exec_ = nullptr;
-    return status_of(e);
-  }
-  graph_ = g;
-  graph_grid_ = grid;
-  graph_block_ = block;
   return MOSS_OK;
 }
 
@@ -233,8 +162,7 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
   if (!scope.ok()) return MOSS_E_DEVICE;
   if (!stream_) {
     if (hipStreamCreateWithFlags(&stream_, hipStreamNonBlocking) != hipSuccess) return MOSS_E_DEVICE;
-    if (hipEventCreate(&ev0_) != hipSuccess || hipEventCreate(&ev1_) != hipSuccess ||
-        hipEventCreateWithFlags(&ev_wait_, hipEventDisableTiming) != hipSuccess ||
+    if (hipEventCreateWithFlags(&ev_wait_, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ev_clear_, hipEventDisableTiming) != hipSuccess)
       return MOSS_E_DEVICE;
   }
@@ -380,33 +308,32 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
     n_tiles += (items[i].k1 - items[i].k0 + T - 1) / T;
     if (n_tiles >= 0xFFFFFFFFull) return MOSS_E_ARG;
   }
-  moss_status st = reserve(views.size(), items.size(), n_slots);
+  // views | items | control words, staged in pinned memory in one piece
+  auto pad = [](size_t n) { return (n + 15) / 16 * 16; };
+  const size_t items_at = pad(views.size() * sizeof(SamplerView));
+  const size_t ctl_at = items_at + pad(items.size() * sizeof(BatchItem)), bytes = ctl_at + pad(4 * sizeof(uint32_t));
+  const uint64_t words = (uint64_t)n_slots * 22;
+  if (words > 0xFFFFFFFFull) return MOSS_E_ARG;
+  moss_status st = reserve(bytes, n_slots);
   if (st != MOSS_OK) return st;
-  st = capture(grid, block);
-  if (st != MOSS_OK) return st;
-
-  // stage views | items | control words in pinned memory and copy in one transfer each
-  unsigned char* p = h_in_;
-  const size_t vbytes = views.size() * sizeof(SamplerView), ibytes = items.size() * sizeof(BatchItem);
-  std::memcpy(p, views.data(), vbytes);
-  BatchItem* ip = (BatchItem*)(p + vbytes);
+  std::memcpy(h_in_, views.data(), views.size() * sizeof(SamplerView));
+  BatchItem* ip = (BatchItem*)(h_in_ + items_at);
   for (size_t i = 0; i < order.size(); ++i) ip[i] = items[order[i]];
-  uint32_t* np = (uint32_t*)(p + vbytes + ibytes);
+  uint32_t* np = (uint32_t*)(h_in_ + ctl_at);
   np[kCtlTiles] = (uint32_t)n_tiles;
   np[kCtlCounter] = 0;
   np[kCtlItems] = (uint32_t)items.size();
   np[kCtlTileSize] = T;
+  auto* host = (unsigned long long*)h_bins_;
+  host[kBatchHostSeq] = 0;  // no launch of an earlier run still writes here
+  const uint64_t seq = ++seq_;
 
   hipError_t e = hipSuccess;
   if (wait_on) {
     e = hipEventRecord(ev_wait_, wait_on);
     if (e == hipSuccess) e = hipStreamWaitEvent(stream_, ev_wait_, 0);
   }
-  if (e == hipSuccess && vbytes) e = hipMemcpyAsync(d_views_, p, vbytes, hipMemcpyHostToDevice, stream_);
-  if (e == hipSuccess && ibytes) e = hipMemcpyAsync(d_items_, p + vbytes, ibytes, hipMemcpyHostToDevice, stream_);
-  if (e == hipSuccess) e = hipMemcpyAsync(d_ctl_, np, 4 * sizeof(uint32_t), hipMemcpyHostToDevice, stream_);
-  if (e == hipSuccess) e = hipEventRecord(ev0_, stream_);
-  if (e == hipSuccess) e = launch_fill_u64((uint64_t*)d_bins_, 0, (int64_t)n_slots * 22, stream_);
+  if (e == hipSuccess) e = launch_batch_stage(h_in_, d_in_, bytes, d_bins_, (uint32_t)words, d_end_, stream_);
   // the grouped launches run on the side streams, beside the persistent kernel (whose
   // latency-bound waves leave block slots and memory bandwidth free), from the clear on;
   // each chunk goes to the chain with less cost so far.  Two chains measured 1%
@@ -415,7 +342,9 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
   const int side = chunks.empty() ? 0 : chains;
   if (e == hipSuccess && side) e = hipEventRecord(ev_clear_, stream_);
   for (int j = 0; j < side && e == hipSuccess; ++j) e = hipStreamWaitEvent(side_[j], ev_clear_, 0);
-  if (e == hipSuccess) e = hipGraphLaunch(exec_, stream_);
+  if (e == hipSuccess && n_tiles > 0)
+    e = launch_batch((const SamplerView*)d_in_, (const BatchItem*)(d_in_ + items_at), (uint32_t*)(d_in_ + ctl_at),
+                     d_bins_, (int)std::min<uint64_t>((uint64_t)grid, n_tiles), block, stream_);
   uint64_t load[2] = {0, 0};
   for (const SortChunk& c : chunks) {
     if (e != hipSuccess) break;
@@ -433,19 +362,26 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
     e = hipEventRecord(ev_side_[j], side_[j]);
     if (e == hipSuccess) e = hipStreamWaitEvent(stream_, ev_side_[j], 0);
   }
-  if (e == hipSuccess) e = hipEventRecord(ev1_, stream_);
-  if (e == hipSuccess && n_slots)
-    e = hipMemcpyAsync(h_bins_, d_bins_, (size_t)n_slots * 22 * sizeof(uint64_t), hipMemcpyDeviceToHost, stream_);
-  if (e == hipSuccess) e = hipStreamSynchronize(stream_);
-  if (e != hipSuccess) {
-    for (int j = 0; j < side; ++j) (void)hipStreamSynchronize(side_[j]);  // nothing of this batch left running
-    return status_of(e);
+  if (e == hipSuccess) e = launch_batch_collect(d_bins_, (uint32_t)words, d_end_, host, seq, stream_);
+  // the slots are in host memory once the sequence number is
+  bool there = false;
+  if (e == hipSuccess) {
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+    do {
+      for (int i = 0; i < 64 && !there; ++i) there = __atomic_load_n(&host[kBatchHostSeq], __ATOMIC_ACQUIRE) == seq;
+    } while (!there && std::chrono::steady_clock::now() < until);
   }
-  std::memcpy(bins_out, h_bins_, (size_t)n_slots * 22 * sizeof(uint64_t));
-  if (device_ms) {
-    float ms = 0.f;
-    *device_ms = hipEventElapsedTime(&ms, ev0_, ev1_) == hipSuccess ? (double)ms : 0.0;
+  if (!there) {
+    if (e == hipSuccess) e = hipStreamSynchronize(stream_);
+    there = e == hipSuccess && __atomic_load_n(&host[kBatchHostSeq], __ATOMIC_ACQUIRE) == seq;
   }
+  if (!there) {  // nothing of this batch left running
+    (void)hipStreamSynchronize(stream_);
+    for (int j = 0; j < side; ++j) (void)hipStreamSynchronize(side_[j]);
+    return e == hipSuccess ? MOSS_E_DEVICE : status_of(e);
+  }
+  std::memcpy(bins_out, host + kBatchHostWords, (size_t)words * sizeof(uint64_t));
+  if (device_ms) *device_ms = (double)host[kBatchHostTicks] / device_ticks_per_ms(device_);
   return MOSS_OK;
 }
 

@@ -16,8 +16,8 @@ struct WorkItem {
   uint32_t slot;
 };
 
-// Device-side state of batched launches on one device: tile list buffers, the
-// per-slot histograms and the captured hipGraph of (clear, persistent kernel).
+// Device-side state of batched launches on one device: the item list's buffers, the
+// per-slot histograms and the streams.
 class BatchRunner {
  public:
   explicit BatchRunner(int device);
@@ -41,24 +41,19 @@ class BatchRunner {
   void release();
 
  private:
-  moss_status reserve(size_t views, size_t items, size_t slots);
-  moss_status capture(int grid, int block);
+  moss_status reserve(size_t bytes, size_t slots);
 
   int device_;
   hipStream_t stream_ = nullptr;
   hipStream_t side_[2] = {};  // the grouped launches in two chains, beside the persistent kernel
-  hipEvent_t ev0_ = nullptr, ev1_ = nullptr, ev_wait_ = nullptr, ev_clear_ = nullptr, ev_side_[2] = {};
-  SamplerView* d_views_ = nullptr;
-  BatchItem* d_items_ = nullptr;
-  uint32_t* d_ctl_ = nullptr;  // control words (kCtl*)
-  unsigned long long* d_bins_ = nullptr;
-  size_t cap_views_ = 0, cap_items_ = 0, cap_slots_ = 0;
-  unsigned char* h_in_ = nullptr;  // pinned staging for views + items + control words
-  size_t cap_in_ = 0;
-  uint64_t* h_bins_ = nullptr;     // pinned, cap_slots_ x 22
-  hipGraph_t graph_ = nullptr;
-  hipGraphExec_t exec_ = nullptr;
-  int graph_grid_ = 0, graph_block_ = 0;
+  hipEvent_t ev_wait_ = nullptr, ev_clear_ = nullptr, ev_side_[2] = {};
+  unsigned char* d_in_ = nullptr;          // views, items, control words (kCtl*)
+  unsigned char* h_in_ = nullptr;          // their pinned staging
+  unsigned long long* d_bins_ = nullptr;   // cap_slots_ x 22 counts
+  unsigned long long* d_end_ = nullptr;    // two words of the collecting kernel
+  uint64_t* h_bins_ = nullptr;             // pinned: kBatchHostWords words, then the counts
+  size_t cap_in_ = 0, cap_slots_ = 0;
+  uint64_t seq_ = 0;                       // runs so far
 };
 
 // The process-wide runner of a device (created on first use).

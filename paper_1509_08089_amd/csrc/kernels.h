@@ -76,8 +76,8 @@ struct BatchItem {
   uint64_t k0, k1;      // sample indices
 };
 
-// Control words of a batched launch: tiles in all, the tile counter (cleared by the
-// launch), items, samples per tile.
+// Control words of a batched launch: tiles in all, the tile counter (0 at first), items,
+// samples per tile.
 constexpr int kCtlTiles = 0, kCtlCounter = 1, kCtlItems = 2, kCtlTileSize = 3;
 
 hipError_t upload_class_luts(const uint8_t lut4[8], const uint8_t lut5t[64], const uint8_t lut5p[64]);
@@ -307,10 +307,18 @@ hipError_t launch_sample_chunk(int sampler, const SamplerView& v, uint64_t seed,
 hipError_t launch_sample_nodes(int sampler, const SamplerView& v, uint64_t seed, const uint64_t* index,
                                int64_t count, int32_t* nodes_out, uint8_t* class_out, hipStream_t s);
 
-// Batched persistent launch over an item list resident in device memory: blocks take
-// tiles from ctl[kCtlCounter] until ctl[kCtlTiles] are drawn, each finding its item.
+// A batch: stage (`bytes` of views, items and control words, a multiple of 16, from pinned
+// host memory; clears `words` histogram words), the persistent launch over the items, on at
+// most as many blocks as tiles, and collect (the histogram words to
+// host[kBatchHostWords ..), the device ticks since the stage and then `seq`).  `end`: two
+// device words of theirs.
+constexpr int kBatchHostSeq = 0, kBatchHostTicks = 1, kBatchHostWords = 2;
+hipError_t launch_batch_stage(const void* host, void* dev, size_t bytes, unsigned long long* bins, uint32_t words,
+                              unsigned long long* end, hipStream_t s);
 hipError_t launch_batch(const SamplerView* views, const BatchItem* items, uint32_t* ctl, unsigned long long* bins,
                         int grid, int block, hipStream_t s);
+hipError_t launch_batch_collect(const unsigned long long* bins, uint32_t words, unsigned long long* end,
+                                unsigned long long* host, uint64_t seq, hipStream_t s);
 
 // Registers/VGPR usage probe for occupancy decisions (max active blocks per CU).
 int sample_kernel_blocks_per_cu(int sampler, int block);

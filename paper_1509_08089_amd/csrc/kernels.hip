@@ -2416,8 +2416,8 @@ __device__ __forceinline__ void flush_hits(const uint32_t (&bins)[kMaxWaves][kBi
     if (s) before = atomicAdd(&part[base + lane], (unsigned long long)s);
   }
   if (!k.add && !k.host) return;  // a later launch hands the counts over
-  // Only device-scope atomics touch the rows, so order is all that is needed and no fence (a
-  // fence a block writes back and drops its caches under the blocks still running: 5% of a
+  // Only read-modify-write atomics touch the rows, so order is all that is needed and no
+  // fence (a fence a block writes back and drops its caches under the blocks still running: 5% of a
   // launch): the counts' atomics have returned before the tickets go out.
   asm volatile("" ::"v"((uint32_t)before) : "memory");
   unsigned long long* all = k.parts + kHitParts * kHitPartWords;
@@ -2431,17 +2431,13 @@ __device__ __forceinline__ void flush_hits(const uint32_t (&bins)[kMaxWaves][kBi
   uint64_t sum = 0;
   if (lane <= kHitTicket) {
 #pragma unroll 8
-    for (int i = 0; i < kHitParts; ++i)
-      sum += __hip_atomic_load(&k.parts[i * kHitPartWords + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll 8
-    for (int i = 0; i < kHitParts; ++i)
-      __hip_atomic_store(&k.parts[i * kHitPartWords + lane], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int i = 0; i < kHitParts; ++i) sum += atomicExch(&k.parts[i * kHitPartWords + lane], 0ull);
   }
-  if (lane == 0) __hip_atomic_store(&all[kHitTicket], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (lane == 0) (void)atomicExch(&all[kHitTicket], 0ull);
   if (k.add && lane < 2 * kBins && sum) atomicAdd(&k.add[lane], (unsigned long long)sum);
   if (k.host) {
     if (lane == kHostTicks)
-      sum = wall_clock64() - __hip_atomic_load(&all[kHitStart], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sum = wall_clock64() - atomicExch(&all[kHitStart], 0ull);
     static_assert(kHostTicks == 2 * kBins, "the ticks follow the counts");
     if (lane <= kHostTicks) __hip_atomic_store(&k.host[lane], (unsigned long long)sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __threadfence_system();
@@ -2452,8 +2448,7 @@ __device__ __forceinline__ void flush_hits(const uint32_t (&bins)[kMaxWaves][kBi
 // The first launch of a call notes when it starts (its block 0).
 __device__ __forceinline__ void stamp_start(unsigned long long* parts, uint32_t first) {
   if (first && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
-    __hip_atomic_store(&parts[kHitParts * kHitPartWords + kHitStart], (unsigned long long)wall_clock64(),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    (void)atomicExch(&parts[kHitParts * kHitPartWords + kHitStart], (unsigned long long)wall_clock64());
 }
 
 // ---------------------------------------------------------------------------------
@@ -3096,17 +3091,58 @@ hipError_t launch_sample_nodes(int sampler, const SamplerView& v, uint64_t seed,
 }
 
 // ---------------------------------------------------------------------------------
-// Persistent batched kernel: blocks take tiles from a shared counter until the list
-// is drained (every block exits once the counter passes n_tiles).  Each tile's
-// samples are spread over the block's lanes; its histogram is flushed to the tile's
-// output slot.  The sampler is uniform within a tile, so the branch is uniform.
+// Batched launches.  k_batch_stage copies the views, items and control words from pinned
+// host memory, clears the histogram slots and notes the start; k_batch draws the tiles;
+// k_batch_collect, after the grouped launches beside it, hands the slots to the host.
+// Three plain launches: a captured graph of the clear and the persistent kernel took 27 us
+// to launch and wait for where two launches take 11, three copies to the device 4 us each,
+// the events around the batch 6 us.
 // ---------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_batch_stage(const uint4* __restrict__ host, uint4* __restrict__ dev,
+                                                     uint32_t quads, unsigned long long* __restrict__ bins,
+                                                     uint32_t words, unsigned long long* __restrict__ end) {
+  const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  for (uint32_t i = i0; i < quads; i += step) dev[i] = host[i];
+  for (uint32_t i = i0; i < words; i += step) bins[i] = 0;
+  if (i0 == 0) {
+    end[0] = 0;  // blocks of k_batch_collect that are done
+    end[1] = (unsigned long long)wall_clock64();
+  }
+}
+
+__global__ __launch_bounds__(256) void k_batch_collect(const unsigned long long* __restrict__ bins, uint32_t words,
+                                                       unsigned long long* __restrict__ end,
+                                                       unsigned long long* __restrict__ host, uint64_t seq) {
+  __shared__ uint32_t last;
+  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x)
+    host[kBatchHostWords + i] = bins[i];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) last = atomicAdd(&end[0], 1ull) == gridDim.x - 1;
+  __syncthreads();
+  if (!last || threadIdx.x != 0) return;
+  __hip_atomic_store(&host[kBatchHostTicks], (unsigned long long)wall_clock64() - end[1], __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&host[kBatchHostSeq], (unsigned long long)seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Persistent kernel: block b takes tile b, then tiles from a shared counter until the list
+// is drained (every block exits once its tile is past n_tiles).  The counter starts at the
+// grid's size: with every block's first tile and its last, failed claim taken from one
+// word, 1536 blocks queued on it twice, 20 us each time.  A tile's number, and with it its
+// item, view and their addresses, are the same for the whole block and known to be (block
+// index, readfirstlane), so the item is searched for with scalar loads by every wave (one
+// thread's search with a barrier, or 64 items compared at a time by vector loads, 1% and 2%
+// slower on 256 requests).  Each tile's samples are spread over the block's lanes; its
+// histogram is flushed to the item's slot.  The sampler is uniform within a tile, so the
+// branch is uniform.  12 requests of 5e3 to 2e5 samples over 4 small graphs 200 -> 143 us,
+// with the launches above.
 __global__ __launch_bounds__(256, kSampleWaves) void k_batch(const SamplerView* __restrict__ views,
                                                const BatchItem* __restrict__ items, uint32_t* ctl,
                                                unsigned long long* __restrict__ bins) {
   __shared__ uint32_t lb[kMaxWaves][kBins + 2];
   __shared__ uint8_t lut4[64], lut5t[64], lut5p[64];
-  __shared__ uint32_t cur, cur_item;
+  __shared__ uint32_t cur;
   __shared__ LaneSort<kLaneChunk> ls;
   const int tid = threadIdx.x, wave = tid >> 6, nw = blockDim.x >> 6;
   if (tid < 64) {
@@ -3116,27 +3152,15 @@ __global__ __launch_bounds__(256, kSampleWaves) void k_batch(const SamplerView* 
   }
   const uint32_t n_tiles = ctl[kCtlTiles], n_items = ctl[kCtlItems], T = ctl[kCtlTileSize];
   uint32_t from = 0;  // tiles come in increasing order, so a block's items never go back
-  for (;;) {
-    if (tid == 0) {
-      const uint32_t t = atomicAdd(&ctl[kCtlCounter], 1u);
-      cur = t;
-      if (t < n_tiles) {  // the last item whose first tile is at or before t
-        uint32_t lo = from, hi = n_items - 1;
-        while (lo < hi) {
-          const uint32_t mid = lo + (hi - lo + 1) / 2;
-          if (items[mid].first_tile <= t) lo = mid;
-          else hi = mid - 1;
-        }
-        cur_item = lo;
-      }
+  for (uint32_t t = blockIdx.x; t < n_tiles;) {
+    uint32_t hi = n_items - 1;  // the last item whose first tile is at or before t
+    while (from < hi) {
+      const uint32_t mid = from + (hi - from + 1) / 2;
+      if (items[mid].first_tile <= t) from = mid;
+      else hi = mid - 1;
     }
     for (int i = tid; i < nw * (kBins + 2); i += blockDim.x) lb[i / (kBins + 2)][i % (kBins + 2)] = 0;
     __syncthreads();
-    // the same for the whole block, and told so: the item, its view and their addresses then
-    // live in scalar registers
-    const uint32_t t = __builtin_amdgcn_readfirstlane(cur);
-    if (t >= n_tiles) break;
-    from = __builtin_amdgcn_readfirstlane(cur_item);
     const BatchItem it = items[from];
     const SamplerView v = views[it.view];
     const uint64_t a = it.k0 + (uint64_t)(t - it.first_tile) * T;
@@ -3150,13 +3174,33 @@ __global__ __launch_bounds__(256, kSampleWaves) void k_batch(const SamplerView* 
       for (int w = 0; w < nw; ++w) s += lb[w][tid];
       if (s) atomicAdd(&bins[(uint64_t)it.out * kBins + tid], (unsigned long long)s);
     }
+    if (n_tiles <= gridDim.x) break;  // every tile has had its block
+    if (tid == 0) cur = gridDim.x + atomicAdd(&ctl[kCtlCounter], 1u);
     __syncthreads();
+    t = __builtin_amdgcn_readfirstlane(cur);
   }
+}
+
+hipError_t launch_batch_stage(const void* host, void* dev, size_t bytes, unsigned long long* bins, uint32_t words,
+                              unsigned long long* end, hipStream_t s) {
+  const uint32_t quads = (uint32_t)(bytes / 16);
+  if (bytes % 16 || bytes / 16 > 0xFFFFFFFFull) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_batch_stage, dim3((unsigned)std::max(1, std::min(fill_grid(std::max(quads, words)), 256))),
+                     dim3(256), 0, s, static_cast<const uint4*>(host), static_cast<uint4*>(dev), quads, bins, words, end);
+  return hipGetLastError();
 }
 
 hipError_t launch_batch(const SamplerView* views, const BatchItem* items, uint32_t* ctl, unsigned long long* bins,
                         int grid, int block, hipStream_t s) {
+  if (grid < 1 || block < 64 || block > 256 || block % 64) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_batch, dim3(grid), dim3(block), 0, s, views, items, ctl, bins);
+  return hipGetLastError();
+}
+
+hipError_t launch_batch_collect(const unsigned long long* bins, uint32_t words, unsigned long long* end,
+                                unsigned long long* host, uint64_t seq, hipStream_t s) {
+  hipLaunchKernelGGL(k_batch_collect, dim3((unsigned)std::max(1, std::min(fill_grid(words), 64))), dim3(256), 0, s,
+                     bins, words, end, host, seq);
   return hipGetLastError();
 }
 

@@ -50,3 +50,17 @@ def test_a_sampler_that_draws_nothing():
     G, og = moss.Graph(g), oracle.Graph(g)
     for k in (4, 5):
         np.testing.assert_array_equal(G.estimate(k, 10_001, 2).hits_np, og.estimate(k, 10_001, 2, threads=2).hits)
+
+
+@pytest.mark.parametrize("requests,budget", [(1, 1), (1, 5_000_000), (3, 257), (65, 300), (700, 600)])
+def test_batch_items_and_tiles(graphs, requests, budget):
+    """One item to more than a thousand, fewer tiles than blocks and more, batch after batch
+    with fewer slots than the one before: each request as alone."""
+    G, og = graphs
+    for count in (requests, max(1, requests // 2)):
+        reqs = [(G.h, 4 + i % 2, budget + i + 1, 40 + i, 0) for i in range(count)]
+        out = moss.moss_estimate_batch(reqs)
+        for i in sorted({0, count // 3, count - 1}):
+            _, k, n, seed, _ = reqs[i]
+            np.testing.assert_array_equal(out[i].hits_np, G.estimate(k, n, seed).hits_np)
+            assert out[i].hits_np.sum() == n and out[i].device_ms > 0
