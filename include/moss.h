@@ -337,7 +337,7 @@ typedef struct {
   uint32_t group_min_footprint_mb;  /* <= 2^20 */
   uint32_t sort_window;             /* samples a block of the sorted sampling kernel takes at
                                        a time (a multiple of 64, <= 512; 0 = 256 on graphs
-                                       past 256 MB of sampled bytes, else 512) */
+                                       past 96 MB of sampled bytes, else 512) */
 } moss_tuning;
 
 moss_status moss_set_tuning(const moss_tuning *t);

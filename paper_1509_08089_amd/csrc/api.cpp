@@ -184,10 +184,11 @@ static int most_blocks(const moss_graph* g, int sampler, bool grouped, int block
   const Tuning t = current_tuning();
   int per_cu = (int)t.blocks_per_cu;
   if (per_cu == 0) {
-    // grouped launches: 28 waves per CU (n = 1e5, m = 1e6, MOSS-4 for 1e7 samples,
-    // 12 / 16 / 20 / 24 / 28 / 32 waves: 0.687 / 0.602 / 0.559 / 0.542 / 0.538 / 0.540
-    // ms; n = 1e6, m = 1e7, T-5 for 5e7: 6.14 / 5.71 / 5.61 / 5.60 / 5.61 / 5.62 ms)
-    const int waves = grouped ? 28 : sampling_waves_per_cu(sampling_footprint(g));
+    // grouped launches: 28 waves per CU within the MALL, 24 beyond (16 / 20 / 24 / 28 waves:
+    // n = 1e5, m = 1e6, MOSS-4 for 1e7 samples, 444 / 418 / 404 / 397 us; m = 1e7, 1e8 5-node
+    // samples, 11.43 / 11.37 / 11.38 / 11.43 ms)
+    const uint64_t fp = sampling_footprint(g);
+    const int waves = !grouped ? sampling_waves_per_cu(fp) : fp > (256ull << 20) ? 24 : 28;
     const int cap = std::max(1, std::min(sample_kernel_blocks_per_cu(sampler, block), 8));
     per_cu = std::max(1, std::min(cap, waves / (block / 64)));
   }

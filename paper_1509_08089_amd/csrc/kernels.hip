@@ -2681,16 +2681,17 @@ constexpr int kOrderBits = 32 - kLaneBits;  // a sample's offset in its chunk
 constexpr uint32_t kOrderMask = (1u << kOrderBits) - 1;
 constexpr uint32_t kSortSpan = 8192;   // samples per block of the counting passes
 static_assert(kSortSpan <= 65536 && kSortSpan % 16 == 0, "16-bit local offsets, 16-byte group loads");
-// Sorted entries a block takes per cursor step: 512 while the sampled tables fit the
-// MALL, 256 beyond it (multiples of the 256-thread block; 128 leaves half the threads
-// idle).  Smaller windows keep the blocks of an XCD closer together in the sorted
-// order, so that they share more of their tables' lines in the L2, as long as the
-// cursor atomics keep up.  Measured with the cursors apart (below): n = 1e6, m = 1e7,
-// T-5 / Path-5 for 5e7 samples each, 5.74 / 8.31 ms at 512, 5.72 / 8.19 at 256,
-// 7.31 / 10.36 at 128; n = 1e5, m = 1e6, MOSS-4 for 1e7 samples, 0.628 ms at 2048,
-// 0.600 at 1024, 0.575 at 512, 0.577 at 256, 0.63 at 384, 0.78 at 128.  A cursor per
-// wave instead of per block (no block barriers) measured 0.61 ms there.
-uint32_t sort_window(uint64_t footprint_bytes) { return footprint_bytes > (256ull << 20) ? 256u : 512u; }
+// Sorted entries a block takes per cursor step: 512 up to 96 MB of sampled tables, 256
+// beyond (multiples of the 256-thread block; 128 leaves half the threads idle).  Smaller
+// windows keep the blocks of an XCD closer together in the sorted order, so that they share
+// more of their tables' lines in the L2, as long as the cursor atomics keep up.  Measured,
+// windows of 128 / 256 / 384 / 512: n = 1e5, m = 1e6, MOSS-4 for 1e7 samples (54 MB) 497 /
+// 406 / 413 / 397 us an estimate; m = 2e6, 8e6 5-node samples (150 MB) 694 / 618 / 643 /
+// 642; m = 3e6, MOSS-4 with MOSS-4Min for 4e6 (200 MB) 366 / 351 / 365 / 377; m = 1e7, 1e8
+// 5-node samples (670 MB) 11.59 / 11.43 / 11.51 / 11.69 ms.  A cursor per wave instead of
+// per block (no block barriers) was slower at m = 1e6, as were blocks of 512 to 1024
+// threads with windows to match.
+uint32_t sort_window(uint64_t footprint_bytes) { return footprint_bytes > (96ull << 20) ? 256u : 512u; }
 
 // The eight window cursors sit 256 bytes apart: packed into one line, every XCD's
 // cursor atomics queued on that line (n = 1e5, m = 1e6, MOSS-4 for 1e7 samples: 0.668
