@@ -321,7 +321,7 @@ T* at(void* base, size_t off) {
 // scan scratch, partials, records
 struct GraphLayout {
   size_t small, hit_parts, slots, filter, items, item_sum, guide_len, tmp[3], partials, rec, span_row, check_part, span_sums,
-      span_groups, group_wrap, hub_filter, bytes;
+      span_groups, group_wrap, hub_filter, bucket_fill, spill, bytes;
 };
 
 GraphLayout graph_layout(int32_t n, int64_t nnz) {
@@ -344,6 +344,9 @@ GraphLayout graph_layout(int32_t n, int64_t nnz) {
   L.span_groups = c.take<uint64_t>((size_t)std::max<int64_t>(1, span_group_count(nnz)));
   L.group_wrap = c.take<uint32_t>((size_t)std::max<int64_t>(1, span_group_count(nnz)));
   L.hub_filter = c.take<uint8_t>((size_t)nnz);
+  const bool buckets = edge_set_by_buckets(nnz / 2, edge_hash_bits(nnz / 2));
+  L.bucket_fill = c.take<uint32_t>(buckets ? (size_t)edge_bucket_count(edge_hash_bits(nnz / 2)) + 1 : 0);
+  L.spill = c.take<uint64_t>(buckets ? kSpillCap : 0);
   L.bytes = c.off;
   return L;
 }
@@ -515,14 +518,37 @@ moss_status finish_create(moss_graph* g) {
   hipStream_t s = g->stream;
   const int64_t cap = items_cap(g->n, g->nnz);
   uint32_t* err = (uint32_t*)(g->small + kWErr);
+  const bool full = !(g->flags & MOSS_TRUST_CSR);
+  bool buckets = edge_set_by_buckets(g->nnz / 2, g->edge_bits);
+  uint32_t* bucket_fill = at<uint32_t>(m, L.bucket_fill);
+  auto edge_set_fills = [&](FillSet* f) {  // what the edge set's compare-and-swaps start from
+    f->p[1] = g->edge_slots;
+    f->count[1] = (int64_t)1 << g->edge_bits;
+    f->value[1] = ~0ull;
+    f->p[2] = g->filter;
+    f->count[2] = (int64_t)1 << g->filter_bits;
+  };
+  auto edge_set_by_swaps = [&]() {
+    hipError_t x = launch_edge_insert(g->nnz, g->span_row, g->rp, g->col, g->n, g->edge_slots, g->edge_bits, g->filter,
+                                      g->filter_bits, g->small, s);
+    if (x == hipSuccess)
+      x = launch_check_items(g->nnz, g->span_row, g->n, g->rp, g->col, full, g->edge_slots, g->edge_bits, g->check_part,
+                             g->small, s);
+    return x;
+  };
+  auto copy_back = [&]() {
+    hipError_t x = hipMemcpyAsync(g->h_stage, g->small, kWBack * sizeof(uint64_t), hipMemcpyDeviceToHost, s);
+    return x == hipSuccess ? hipStreamSynchronize(s) : x;
+  };
   FillSet f{};
   f.p[0] = g->small;
   f.count[0] = kWords;
-  f.p[1] = g->edge_slots;
-  f.count[1] = (int64_t)1 << g->edge_bits;
-  f.value[1] = ~0ull;
-  f.p[2] = g->filter;
-  f.count[2] = (int64_t)1 << g->filter_bits;
+  if (buckets) {  // the layout rounds its arrays up to 256 bytes
+    f.p[1] = (uint64_t*)bucket_fill;
+    f.count[1] = (edge_bucket_count(g->edge_bits) + 2) / 2;
+  } else {
+    edge_set_fills(&f);
+  }
   f.p[3] = (uint64_t*)g->hit_parts;
   f.count[3] = kHitPartsWords;
   hipError_t e = launch_fill_set(f, s);
@@ -544,13 +570,20 @@ moss_status finish_create(moss_graph* g) {
     e = launch_items_records(g->n, g->nnz, g->rp, g->item_sum, g->guide_len, cap, g->items, g->rec, g->span_row,
                              g->small, s);
   if (e == hipSuccess)
-    e = launch_edge_insert(g->nnz, g->span_row, g->rp, g->col, g->n, g->edge_slots, g->edge_bits, g->filter,
-                           g->filter_bits, g->small, s);
-  if (e == hipSuccess)
-    e = launch_check_items(g->nnz, g->span_row, g->n, g->rp, g->col, !(g->flags & MOSS_TRUST_CSR), g->edge_slots,
-                           g->edge_bits, g->check_part, g->small, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(g->h_stage, g->small, 8 * sizeof(uint64_t), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+    e = buckets ? launch_edge_buckets(g->nnz, g->span_row, g->n, g->rp, g->col, full, g->edge_slots, g->edge_bits,
+                                      g->filter, g->filter_bits, bucket_fill, at<uint64_t>(m, L.spill), kSpillCap,
+                                      g->check_part, g->small, s)
+                : edge_set_by_swaps();
+  if (e == hipSuccess) e = copy_back();
+  if (e == hipSuccess && buckets && g->h_stage[kWBucketFull]) {  // keys crowded into few buckets: the general way
+    FillSet again{};
+    edge_set_fills(&again);
+    again.p[0] = g->small + kWErr;  // the checks run again
+    again.count[0] = 1;
+    e = launch_fill_set(again, s);
+    if (e == hipSuccess) e = edge_set_by_swaps();
+    if (e == hipSuccess) e = copy_back();
+  }
   if (e != hipSuccess) return status_of(e);
   const uint64_t* h = g->h_stage;
   uint32_t bits = (uint32_t)(h[kWErr] & 0xFFFFFFFFu);
@@ -559,7 +592,7 @@ moss_status finish_create(moss_graph* g) {
   g->n_items = (int64_t)h[kWItems];
   g->row_guide_len = (int64_t)h[kWGuideLen];
   if (g->n_items > cap) return MOSS_E_ARG;
-  if (!(g->flags & MOSS_TRUST_CSR) && 2 * h[kWUpper] != (uint64_t)g->nnz) return MOSS_E_ASYMMETRIC;
+  if (full && 2 * h[kWUpper] != (uint64_t)g->nnz) return MOSS_E_ASYMMETRIC;
   return MOSS_OK;
 }
 

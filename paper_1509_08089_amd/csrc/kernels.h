@@ -57,6 +57,7 @@ constexpr int kWItems = 4;     // number of work items
 constexpr int kWGuideLen = 5;  // entries of one row-guide array
 constexpr int kWUpper = 6;     // CSR entries (v, c) with c > v
 constexpr int kWMaxDeg = 7;    // largest degree
+constexpr int kWBucketFull = 12;  // the edge set's buckets did not hold its keys
 constexpr int kWTotal = 8;     // totals of the Gamma, Gamma^(1), Gamma^(2), check-Gamma node weights
 constexpr int kWBack = 16;     // words copied back after a table build
 constexpr int kWords = 64;
@@ -133,6 +134,21 @@ hipError_t launch_items_records(int32_t n, int64_t nnz, const int32_t* rp, const
 hipError_t launch_edge_insert(int64_t nnz, const int32_t* span_row, const int32_t* rp, const int32_t* col, int32_t n,
                               uint64_t* slots, int hash_bits, uint64_t* filter, int filter_bits, uint64_t* small,
                               hipStream_t s);
+// The edge set, the filter and the checks of launch_check_items by buckets, for graphs of at
+// least kBucketMinEdges edges whose set has at most 2^kMaxBucketBits buckets.  `fill`:
+// edge_bucket_count + 1 words, zeroed beforehand; `spill`: spill_cap words.  Neither the
+// slots nor the filter need clearing.  small[kWBucketFull] is set when some bucket or the
+// list did not hold its keys; the set is then built by launch_edge_insert instead.
+constexpr int64_t kBucketMinEdges = 1 << 17;
+constexpr int kMaxBucketBits = 14;
+constexpr uint32_t kSpillCap = 1u << 16;
+bool edge_set_by_buckets(int64_t m, int hash_bits);
+int64_t edge_bucket_count(int hash_bits);
+hipError_t launch_edge_buckets(int64_t nnz, const int32_t* span_row, int32_t n, const int32_t* rp, const int32_t* col,
+                               bool full, uint64_t* slots, int hash_bits, uint64_t* filter, int filter_bits,
+                               uint32_t* fill, uint64_t* spill, uint32_t spill_cap, uint64_t* part, uint64_t* small,
+                               hipStream_t s);
+
 // Column range; with `full` also self-loops, strict ascent and, through the hash set,
 // the mirror of every entry (v, c) with c < v; counts the entries with c > v into
 // small[kWUpper] (through part: check_part_words() u64 of per-block counts).
