@@ -890,8 +890,7 @@ moss_status moss::build_tables(moss_graph* g, uint32_t k_mask) {
   }
   if (e == hipSuccess && (want4 || want5))
     e = launch_node_weights(g->n, g->rp, g->rec, want5 ? g->acc_tau : nullptr, want4 ? g->acc_node[0] : nullptr,
-                            want5 ? g->acc_node[1] : nullptr, want5 ? g->acc_node[2] : nullptr, g->partials,
-                            (unsigned long long*)(g->small + kWLambda), err, s);
+                            want5 ? g->acc_node[1] : nullptr, want5 ? g->acc_node[2] : nullptr, g->partials, err, s);
   ScanSet scans{};
   GuideSet guides{};
   for (int slot = 0; slot < 3; ++slot) {
@@ -906,6 +905,10 @@ moss_status moss::build_tables(moss_graph* g, uint32_t k_mask) {
     guides.count = scans.count;
   }
   if (e == hipSuccess) e = launch_scans(scans, g->n, err, s);
+  guides.partials = g->partials;
+  guides.partial_blocks = node_weight_blocks(g->n);
+  guides.lambdas = (unsigned long long*)(g->small + kWLambda);
+  guides.err = err;
   if (e == hipSuccess) e = launch_guides(guides, g->n, g->gbits, s);
   if (want_min) {
     // ranks (the row prefix array serves as their scratch), the prefix of

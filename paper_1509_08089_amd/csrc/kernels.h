@@ -231,19 +231,25 @@ hipError_t launch_hub_filter(int64_t nnz, const int32_t* span_row, const uint4* 
                              hipStream_t s);
 
 // Node weights (any output may be null) from the node records' S_v and the ACC_tau row
-// ends, and Lambda_3, Lambda_4 into lambdas[0..1]; partials must hold
-// 2 * node_weight_blocks(n) u64.
+// ends, and the blocks' parts of Lambda_3 and Lambda_4 into partials, which must hold
+// 2 * node_weight_blocks(n) u64 (launch_guides adds them up).
 int node_weight_blocks(int32_t n);
 hipError_t launch_node_weights(int32_t n, const int32_t* rp, const uint4* rec, const uint64_t* acc_tau,
                                uint64_t* w_gamma, uint64_t* w_gamma1, uint64_t* w_gamma2, uint64_t* partials,
-                               unsigned long long* lambdas, uint32_t* err, hipStream_t s);
+                               uint32_t* err, hipStream_t s);
 
 // Node-draw guides of up to three scanned weight arrays; total[j] receives acc[j][n-1].
+// With `partials`, also the sums of their partial_blocks pairs into lambdas[0..1], and an
+// overflow's bits into *err.
 struct GuideSet {
   const uint64_t* acc[3];
   uint32_t* guide[3];
   uint64_t* total[3];
   int count;
+  const uint64_t* partials;
+  int partial_blocks;
+  unsigned long long* lambdas;
+  uint32_t* err;
 };
 hipError_t launch_guides(const GuideSet& set, int32_t n, int gbits, hipStream_t s);
 

@@ -10,7 +10,7 @@
 //                      MOSS-4Min row weights, restarted at every row start
 //   k_span_finish      adds the earlier spans' sums to rows that began before the
 //                      span, writes the row guides and S_v
-//   k_node_weights     Gamma_v, Gamma^(1)_v, Gamma^(2)_v, Lambda_3, Lambda_4
+//   k_node_weights     Gamma_v, Gamma^(1)_v, Gamma^(2)_v, blocks' parts of Lambda_3, Lambda_4
 //   k_scan_*           node-level inclusive prefixes ACC_Gamma*
 //   k_guides           search windows for the node draws
 // Sampling (Algorithms 1, 3, 4):
@@ -747,7 +747,9 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_build(uint64_t* __res
                                                                  uint64_t* __restrict__ filter, int filter_bits,
                                                                  const uint32_t* __restrict__ fill,
                                                                  uint64_t* __restrict__ spill, uint32_t spill_cap,
-                                                                 uint32_t* __restrict__ spilled, uint64_t* small) {
+                                                                 uint32_t* __restrict__ spilled,
+                                                                 const uint64_t* __restrict__ part, int parts,
+                                                                 uint64_t* small) {
   __shared__ unsigned long long table[kBucket];
   __shared__ uint32_t words[2 * (kBucket >> 3)];  // the bucket's filter words, in halves
   __shared__ unsigned long long out[kBucketSpill];
@@ -764,6 +766,12 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_build(uint64_t* __res
   for (uint32_t i = tid; i < 2 * nwords; i += kBucketThreads) words[i] = 0;
   __syncthreads();
   if (s_skip) return;
+  if (blockIdx.x == 0 && tid < 64) {  // the upper entries counted by k_edge_bucket's blocks
+    uint64_t x = 0;
+    for (int b = tid; b < parts; b += 64) x += part[b];
+    x = wave_sum(x);
+    if (tid == 0) small[kWUpper] = x;
+  }
   uint64_t* home = slots + (uint64_t)blockIdx.x * kBucket;
   const uint32_t count = fill[blockIdx.x];
   uint64_t key[kBucketKeys];
@@ -860,9 +868,8 @@ hipError_t launch_edge_buckets(int64_t nnz, const int32_t* span_row, int32_t n, 
   const int grid = (int)std::min<int64_t>(chunks, kCheckBlocks);
   hipLaunchKernelGGL(k_edge_bucket, dim3(grid), dim3(kBucketThreads), buckets * sizeof(uint32_t), s, nnz, span_row, n,
                      rp, col, full ? 1 : 0, slots, hash_bits, fill, part, small);
-  hipLaunchKernelGGL(k_check_sum, dim3(1), dim3(256), 0, s, part, grid, small);
   hipLaunchKernelGGL(k_bucket_build, dim3(buckets), dim3(kBucketThreads), 0, s, slots, hash_bits, filter, filter_bits,
-                     fill, spill, spill_cap, fill + buckets, small);
+                     fill, spill, spill_cap, fill + buckets, part, grid, small);
   hipLaunchKernelGGL(k_bucket_spill, dim3(8), dim3(256), 0, s, (unsigned long long*)slots, hash_bits, spill, spill_cap,
                      fill + buckets, small);
   return hipGetLastError();
@@ -978,7 +985,8 @@ __global__ __launch_bounds__(256) void k_span_prefix(RowTables t, uint32_t* err)
     for (int k = 0; k < kPer; ++k) {
       const bool valid = S + lane + 64 * k < t.nnz;
       if (M == kRowSigma) {  // d_x - 1 of the neighbour x
-        x[k] = valid ? (uint64_t)row_of(t.rec, (int32_t)raw[k]).y - 1 : 0ull;
+        const uint2 ends = load_pair(t.rp + (valid ? (int32_t)raw[k] : 0));  // (130 us at m = 1e7; from the node records, four times the bytes, 192)
+        x[k] = valid ? (uint64_t)(ends.y - ends.x) - 1 : 0ull;
       } else if (M == kRowTau) {  // (d_x - 1)(S_v - (d_x - 1)), d_x - 1 from the sigma prefix
         const uint64_t p = __shfl(raw[k], (lane + 63) & 63, 64);
         const uint64_t wrap = k ? __shfl(raw[k > 0 ? k - 1 : 0], 63, 64) : before_span;
@@ -2110,7 +2118,7 @@ int edge_filter_bits(int64_t m) {
 //   Gamma^(2)_v = ACC_tau at the row end = S_v^2 - sum (d_x - 1)^2 (Section 5.1.2)
 //   Lambda_3 = sum C(d_v, 3), Lambda_4 = sum C(d_v, 4)        (Table 1)
 // The Lambdas are reduced per block into `partials` (2 per block) and finished by
-// k_lambda_final, so no two blocks update the same word.
+// k_guides, so no two blocks update the same word.
 // ---------------------------------------------------------------------------------
 constexpr int kWeightThreads = 256;
 
@@ -2168,8 +2176,9 @@ __global__ __launch_bounds__(256) void k_node_weights(int32_t n, const int32_t* 
   }
 }
 
-__global__ __launch_bounds__(256) void k_lambda_final(const uint64_t* __restrict__ partials, int nblocks,
-                                                      unsigned long long* __restrict__ lambdas, uint32_t* err) {
+// Sums the blocks' partial Lambdas (a block of 256 threads, the last row of k_guides).
+__device__ void lambda_final(const uint64_t* __restrict__ partials, int nblocks,
+                             unsigned long long* __restrict__ lambdas, uint32_t* err) {
   __shared__ uint64_t red[2][4];
   bool o4 = false, o5 = false;
   uint64_t a = 0, b = 0;
@@ -2206,12 +2215,11 @@ int node_weight_blocks(int32_t n) { return std::max(1, std::min(2048, (int)((n +
 
 hipError_t launch_node_weights(int32_t n, const int32_t* rp, const uint4* rec, const uint64_t* acc_tau,
                                uint64_t* w_gamma, uint64_t* w_gamma1, uint64_t* w_gamma2, uint64_t* partials,
-                               unsigned long long* lambdas, uint32_t* err, hipStream_t s) {
+                               uint32_t* err, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int nb = node_weight_blocks(n);
   hipLaunchKernelGGL(k_node_weights, dim3(nb), dim3(kWeightThreads), 0, s, n, rp, rec, acc_tau, w_gamma,
                      w_gamma1, w_gamma2, partials, err);
-  hipLaunchKernelGGL(k_lambda_final, dim3(1), dim3(256), 0, s, partials, nb, lambdas, err);
   return hipGetLastError();
 }
 
@@ -2318,20 +2326,40 @@ hipError_t launch_scans(const ScanSet& set, int64_t n, uint32_t* err, hipStream_
 // monotone in the word, so every word of bucket b picks a node in
 // [guide[b], guide[b+1]], and the search runs over that window only.
 // ---------------------------------------------------------------------------------
-__global__ void k_guides(GuideSet set, int32_t n, int gbits) {
+// A thread takes 2^run buckets in a row, the first by a binary search over all nodes, the
+// others by steps on from the one before, doubling (there is about half a node to a
+// bucket): three tables at n = 1e6 77 us with a search for every bucket, 52 with runs of 8;
+// small tables keep a thread to a bucket, whose chains are shorter.
+__global__ __launch_bounds__(256) void k_guides(GuideSet set, int32_t n, int gbits, int run) {
   const int j = blockIdx.y;
+  if (j == set.count) {
+    if (blockIdx.x == 0) lambda_final(set.partials, set.partial_blocks, set.lambdas, set.err);
+    return;
+  }
   const uint64_t* __restrict__ acc = set.acc[j];
   uint32_t* __restrict__ guide = set.guide[j];
   const int64_t G = 1ll << gbits;
   const uint64_t total = acc[n - 1];
   if (blockIdx.x == 0 && threadIdx.x == 0 && set.total[j]) *set.total[j] = total;
   if (total == 0) return;  // nothing can be drawn; the guide is never read
-  for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b <= G; b += (int64_t)gridDim.x * blockDim.x) {
-    if (b == G) {
-      guide[b] = (uint32_t)(n - 1);
-    } else {
+  for (int64_t b0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) << run; b0 <= G;
+       b0 += ((int64_t)gridDim.x * blockDim.x) << run) {
+    int32_t at = 0, hi = n - 1;  // the bucket's node lies in [at, hi]
+    for (int64_t b = b0; b < b0 + (1 << run) && b <= G; ++b) {
+      if (b == G) {
+        guide[b] = (uint32_t)(n - 1);
+        break;
+      }
       const uint64_t r = bounded((uint64_t)b << (64 - gbits), total);
-      guide[b] = (uint32_t)first_above(acc, 0, n - 1, r);
+      if (b > b0) {
+        hi = at;
+        for (int32_t step = 1; acc[hi] <= r; step *= 2) {  // ends: acc[n - 1] = total > r
+          at = hi + 1;
+          hi = n - 1 - hi > step ? hi + step : n - 1;
+        }
+      }
+      at = first_above(acc, at, hi, r);
+      guide[b] = (uint32_t)at;
     }
   }
 }
@@ -2340,7 +2368,9 @@ hipError_t launch_guides(const GuideSet& set, int32_t n, int gbits, hipStream_t 
   if (n <= 0 || set.count <= 0) return hipSuccess;
   if (set.count > 3) return hipErrorInvalidValue;
   const int64_t G = (1ll << gbits) + 1;
-  hipLaunchKernelGGL(k_guides, dim3(fill_grid(G), set.count), dim3(256), 0, s, set, n, gbits);
+  const int run = std::max(0, std::min(3, gbits - 18));
+  hipLaunchKernelGGL(k_guides, dim3(fill_grid((G >> run) + 1), set.count + (set.partials ? 1 : 0)), dim3(256), 0, s,
+                     set, n, gbits, run);
   return hipGetLastError();
 }
 
