@@ -302,8 +302,7 @@ __device__ __forceinline__ void span_rows(const int32_t* __restrict__ rp, int64_
   static_assert(kSpan == 256, "four offsets per lane below");
   const uint4 h = reinterpret_cast<const uint4*>(hist)[lane];
   const uint32_t a = h.x, b = a + h.y, c = b + h.z, d = c + h.w;
-  bool unused = false;
-  const uint32_t before = (uint32_t)(wave_inclusive_scan((uint64_t)d, unused) - d);
+  const uint32_t before = wave_scan32(d) - d;
   wave_lds_sync();
   reinterpret_cast<uint4*>(hist)[lane] =
       make_uint4((before + a) << 1 | (h.x != 0), (before + b) << 1 | (h.y != 0), (before + c) << 1 | (h.z != 0),
@@ -885,31 +884,23 @@ int check_part_words() { return kCheckBlocks; }
 // the row total of ACC_sigma; the MOSS-4Min entries are d_{v,x} d_{x,v} from the rank
 // tables.
 // ---------------------------------------------------------------------------------
-// Each lane owns nb guide entries guide[goff + b0 ..) to set to val; the wave shares the
-// stores out evenly (one entry of a row can own thousands of buckets while its
-// neighbours own none), consecutive lanes writing consecutive entries of one owner.
-// Uniform control flow.
+// Each lane owns nb guide entries guide[goff + b0 ..) to set to val.  Most own none, one or
+// two, which they store; one entry of a row can own thousands, and those go out by the
+// whole wave, owner after owner.  (Sharing all stores out evenly, by a prefix over the
+// lanes and a search for each store's owner, took 60 of a span's 91 LDS operations:
+// k_span_finish 131 to 148 us at m = 1e7, 98 to 117 now.)  Uniform control flow.
 __device__ __forceinline__ void wave_fill_guides(uint32_t* __restrict__ guide, uint32_t goff, uint32_t b0,
                                                  uint32_t nb, uint32_t val) {
-  if (__ballot(nb != 0) == 0) return;  // wave-uniform
-  const int lane = lane_id();
-  uint32_t incl = nb;
+  constexpr uint32_t kOwn = 2;
+  const uint32_t start = goff + b0;
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += y;
-  }
-  const uint32_t total = __shfl(incl, 63, 64);
-  const uint32_t start = goff + b0 - (incl - nb);  // owner's bucket of store index t: start + t
-  for (uint32_t base = 0; base < total; base += 64) {
-    const uint32_t t = base + lane;
-    int j = 0;  // the owner: the first lane whose inclusive count exceeds t
-#pragma unroll
-    for (int step = 32; step > 0; step >>= 1)
-      if (__shfl(incl, j + step - 1, 64) <= t) j += step;
-    const uint32_t at = __shfl(start, j & 63, 64) + t;
-    const uint32_t v = __shfl(val, j & 63, 64);
-    if (t < total) guide[at] = v;
+  for (uint32_t t = 0; t < kOwn; ++t)
+    if (nb > t) guide[start + t] = val;
+  for (uint64_t more = __ballot(nb > kOwn); more; more &= more - 1) {
+    const int j = __ffsll((unsigned long long)more) - 1;
+    const uint32_t at = __builtin_amdgcn_readlane(start, j), count = __builtin_amdgcn_readlane(nb, j);
+    const uint32_t v = __builtin_amdgcn_readlane(val, j);
+    for (uint32_t t = kOwn + lane_id(); t < count; t += 64) guide[at + t] = v;
   }
 }
 
@@ -928,17 +919,12 @@ __device__ __forceinline__ uint32_t row_overflow_bit() {
 // on return `head` tells whether a restart lies at or before the lane.  `wrapped` is
 // set on any 64-bit wrap.
 __device__ __forceinline__ uint64_t wave_segmented_scan(uint64_t x, bool& head, bool& wrapped) {
-  const int lane = lane_id();
   uint32_t f = head ? 1u : 0u;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint64_t y = __shfl_up(x, off, 64);
-    const uint32_t g = __shfl_up(f, off, 64);
-    if (lane >= off) {
-      if (!f) x = add_wrap(y, x, wrapped);
-      f |= g;
-    }
-  }
+  wave_scan_steps([&](auto from) {  // 0 where no lane is to be added
+    const uint32_t lo = from((uint32_t)x), hi = from((uint32_t)(x >> 32)), g = from(f);
+    x = add_wrap(f ? 0ull : (uint64_t)hi << 32 | lo, x, wrapped);
+    f |= g;
+  });
   head = f != 0;
   return x;
 }
@@ -1678,8 +1664,7 @@ __device__ void rank_row_block(int32_t r0, int32_t d, int passes, const int32_t*
       uint32_t tot = 0;
       if (t < 256)
         for (int q = 0; q < kWaves; ++q) tot += hist[q][t];
-      bool unused = false;
-      const uint32_t incl = (uint32_t)wave_inclusive_scan((uint64_t)tot, unused);
+      const uint32_t incl = wave_scan32(tot);
       if (t < 256 && lane == 63) wave_tot[w] = incl;
       __syncthreads();
       if (t < 256) {
@@ -1843,8 +1828,7 @@ __global__ __launch_bounds__(kMirWaves * 64) void k_mirror_scatter(int64_t nnz, 
     uint32_t sum = 0;
     if (i < kMirD)
       for (int q = 0; q < kMirWaves; ++q) sum += hist[q][i];
-    bool unused = false;
-    const uint32_t incl = (uint32_t)wave_inclusive_scan((uint64_t)sum, unused);
+    const uint32_t incl = wave_scan32(sum);
     if (lane == 63) wave_tot[w] = incl;
     __syncthreads();
     if (i < kMirD) {
@@ -1887,8 +1871,7 @@ __global__ __launch_bounds__(kMirWaves * 64) void k_mirror_scatter(int64_t nnz, 
 // wave_tot[4]; returns synchronised.
 __device__ __forceinline__ uint32_t block_exclusive_256(uint32_t x, uint32_t* wave_tot, uint32_t& total) {
   const int lane = lane_id(), w = threadIdx.x >> 6;
-  bool unused = false;
-  const uint32_t incl = (uint32_t)wave_inclusive_scan((uint64_t)x, unused);
+  const uint32_t incl = wave_scan32(x);
   if (lane == 63) wave_tot[w] = incl;
   __syncthreads();
   uint32_t before = 0;
@@ -2778,8 +2761,7 @@ __device__ void lane_sort(LaneSort<N>& ls, uint64_t seed, F index_of, uint32_t n
   if (tid < kLaneBuckets / 4) {  // exclusive prefix of the counts, four per lane of wave 0
     const uint4 c = reinterpret_cast<const uint4*>(ls.start)[tid];
     const uint32_t sum = c.x + c.y + c.z + c.w;
-    bool unused = false;
-    const uint32_t b = (uint32_t)(wave_inclusive_scan(sum, unused) - sum);
+    const uint32_t b = wave_scan32(sum) - sum;
     reinterpret_cast<uint4*>(ls.start)[tid] = make_uint4(b, b + c.x, b + c.x + c.y, b + c.x + c.y + c.z);
   }
   __syncthreads();
