@@ -617,7 +617,10 @@ hipError_t launch_check_items(int64_t nnz, const int32_t* span_row, int32_t n, c
 //   k_edge_bucket    the checks of single entries; every entry's key, a lower entry's
 //                    marked, goes to the bucket of its home slot, into the bucket's own
 //                    stretch of the slot array (a block counts its keys per bucket in LDS,
-//                    reserves their places with one atomic per bucket, and writes them)
+//                    reserves their places with one atomic per bucket, puts the keys in
+//                    bucket order in LDS and writes them out in that order: some four to a
+//                    bucket at m = 1e7, so a wave's store is 16 runs, not 64 single keys.
+//                    Bound by those writes: 20 million single keys 282 us, in runs 172)
 //   k_bucket_build   a block takes a bucket's keys into registers, inserts the upper ones
 //                    in LDS, looks the lower ones' mirrors up there, and writes its slots
 //                    over the keys, and the bucket's filter words
@@ -629,25 +632,29 @@ hipError_t launch_check_items(int64_t nnz, const int32_t* span_row, int32_t n, c
 // k_edge_insert, which holds for keys of any distribution.
 // Against fills of the table, k_edge_insert, k_filter_build and k_check_items (random
 // compare-and-swaps at 2e10 and lookups at 4e10 a second), creation at m = 2e5 / 1e6 / 3e6 /
-// 1e7 89 / 148 / 311 / 905 -> 78 / 90 / 167 / 444 us; at m = 1e5 no difference, 75 us.
+// 1e7 89 / 148 / 311 / 905 -> 71 / 86 / 131 / 330 us; at
+// m = 1e5 no difference.
 constexpr int kBucketBits = 13;
 constexpr uint32_t kBucket = 1u << kBucketBits;
 constexpr int kBucketThreads = 1024;
 constexpr int kBucketKeys = kBucket / kBucketThreads;  // keys of a full bucket per thread
-constexpr int64_t kBucketSpans = 64;                   // spans a block of k_edge_bucket takes at a time
+constexpr uint32_t kFewBuckets = 4096;                 // up to here a block stages 64 spans' keys (128 KB), else 32
 constexpr uint64_t kLowerMark = 1ull << 63;            // ids are below 2^31: no key has this bit
 constexpr uint32_t kBucketSpill = 64;                  // spilled keys a block lists in LDS
 
+template <int Spans, uint32_t MostBuckets>
 __global__ __launch_bounds__(kBucketThreads) void k_edge_bucket(int64_t nnz, const int32_t* __restrict__ span_row,
                                                                 int32_t n, const int32_t* __restrict__ rp,
                                                                 const int32_t* __restrict__ col, int full,
                                                                 uint64_t* __restrict__ slots, int hash_bits,
                                                                 uint32_t* __restrict__ fill,
                                                                 uint64_t* __restrict__ part, uint64_t* small) {
-  extern __shared__ uint32_t lds[];  // the buckets' counts, then their places in this block's reservation
+  extern __shared__ uint32_t lds[];  // per bucket: its keys here, their place in `stage`, from there to its stretch
   __shared__ uint32_t s_bad, s_skip, s_full;
   __shared__ unsigned long long s_upper;
-  __shared__ __align__(16) uint32_t hist[kBucketThreads / 64][kSpan];
+  __shared__ __align__(16) uint64_t stage[Spans * kSpan];  // the block's keys, bucket after bucket
+  __shared__ uint32_t wave_keys[kBucketThreads / 64];
+  static_assert(Spans >= 8 && Spans % (kBucketThreads / 64) == 0, "stage holds the waves' row histograms first");
   const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
   if (tid == 0) {
     s_bad = 0;
@@ -657,11 +664,13 @@ __global__ __launch_bounds__(kBucketThreads) void k_edge_bucket(int64_t nnz, con
   }
   __syncthreads();
   if (s_skip) return;
-  constexpr int kPer = kSpanPer, kWaveSpans = (int)kBucketSpans / (kBucketThreads / 64);
+  constexpr int kPer = kSpanPer, kWaveSpans = Spans / (kBucketThreads / 64);
+  constexpr int kOwn = MostBuckets > kBucketThreads ? (int)(MostBuckets / kBucketThreads) : 1;  // a thread's buckets
+  uint32_t* hist = reinterpret_cast<uint32_t*>(stage) + wave * kSpan;
   const uint32_t buckets = 1u << (hash_bits - kBucketBits);
   const int64_t spans = (nnz + kSpan - 1) / kSpan;
   uint32_t bad = 0, upper = 0;
-  for (int64_t sp0 = (int64_t)blockIdx.x * kBucketSpans; sp0 < spans; sp0 += (int64_t)gridDim.x * kBucketSpans) {
+  for (int64_t sp0 = (int64_t)blockIdx.x * Spans; sp0 < spans; sp0 += (int64_t)gridDim.x * Spans) {
     for (uint32_t b = tid; b < buckets; b += kBucketThreads) lds[b] = 0;
     __syncthreads();
     uint64_t key[kWaveSpans][kPer];  // all ones: none
@@ -678,7 +687,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_edge_bucket(int64_t nnz, con
 #pragma unroll
       for (int k = 0; k < kPer; ++k) c[k] = S + lane + 64 * k < nnz ? col[S + lane + 64 * k] : 0;
       const int32_t before_span = (lane == 0 && S > 0) ? col[S - 1] : 0;
-      span_rows(rp, S, span_row[sp], span_row[sp + 1], hist[wave], row, head);
+      span_rows(rp, S, span_row[sp], span_row[sp + 1], hist, row, head);
 #pragma unroll
       for (int k = 0; k < kPer; ++k) {
         // the previous entry's column: lane l - 1's, lane 63's of the previous round, or the
@@ -706,24 +715,51 @@ __global__ __launch_bounds__(kBucketThreads) void k_edge_bucket(int64_t nnz, con
       }
     }
     __syncthreads();
-    for (uint32_t b = tid; b < buckets; b += kBucketThreads) {
-      const uint32_t count = lds[b];
-      if (count == 0) continue;
-      const uint32_t at = atomicAdd(&fill[b], count);
-      lds[b] = at;
-      if (at + count > kBucket || at + count < at) s_full = 1;
+    uint32_t count[kOwn], at[kOwn], mine = 0;  // reserve; the places come back during the scan
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+      const uint32_t b = tid + i * kBucketThreads;
+      count[i] = b < buckets ? lds[b] : 0u;
+      at[i] = count[i] ? atomicAdd(&fill[b], count[i]) : 0u;
+      mine += count[i];
+    }
+    const uint32_t incl = wave_scan32(mine);
+    if (lane == 63) wave_keys[wave] = incl;
+    __syncthreads();
+    uint32_t start = incl - mine, total = 0;
+    for (int w = 0; w < kBucketThreads / 64; ++w) {
+      if (w < wave) start += wave_keys[w];
+      total += wave_keys[w];
+    }
+    uint32_t from = start;
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+      if (count[i]) lds[tid + i * kBucketThreads] = from;
+      from += count[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kWaveSpans; ++q)
+#pragma unroll
+      for (int k = 0; k < kPer; ++k)
+        if (key[q][k] != kEmptySlot)
+          stage[lds[edge_slot(key[q][k] & ~kLowerMark, hash_bits) >> kBucketBits] + rank[q][k]] = key[q][k];
+    __syncthreads();
+    from = start;
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+      if (count[i]) lds[tid + i * kBucketThreads] = at[i] - from;
+      if (at[i] + count[i] > kBucket || at[i] + count[i] < at[i]) s_full = 1;
+      from += count[i];
     }
     __syncthreads();
     const bool skip = s_full != 0;  // some bucket is full: the set is built the other way
     if (!skip) {
-#pragma unroll
-      for (int q = 0; q < kWaveSpans; ++q)
-#pragma unroll
-        for (int k = 0; k < kPer; ++k) {
-          if (key[q][k] == kEmptySlot) continue;
-          const uint32_t b = (uint32_t)(edge_slot(key[q][k] & ~kLowerMark, hash_bits) >> kBucketBits);
-          slots[(uint64_t)b * kBucket + lds[b] + rank[q][k]] = key[q][k];
-        }
+      for (uint32_t i = tid; i < total; i += kBucketThreads) {
+        const uint64_t e = stage[i];
+        const uint32_t b = (uint32_t)(edge_slot(e & ~kLowerMark, hash_bits) >> kBucketBits);
+        slots[(uint64_t)b * kBucket + (uint32_t)(lds[b] + i)] = e;
+      }
     }
     __syncthreads();  // the counts are cleared again
     if (skip) break;
@@ -863,10 +899,16 @@ hipError_t launch_edge_buckets(int64_t nnz, const int32_t* span_row, int32_t n, 
   if (hash_bits < kBucketBits || hash_bits - kBucketBits > kMaxBucketBits || shift < 3 || shift > kBucketBits)
     return hipErrorInvalidValue;
   const uint32_t buckets = (uint32_t)edge_bucket_count(hash_bits);
-  const int64_t chunks = (span_count(nnz) + kBucketSpans - 1) / kBucketSpans;
-  const int grid = (int)std::min<int64_t>(chunks, kCheckBlocks);
-  hipLaunchKernelGGL(k_edge_bucket, dim3(grid), dim3(kBucketThreads), buckets * sizeof(uint32_t), s, nnz, span_row, n,
-                     rp, col, full ? 1 : 0, slots, hash_bits, fill, part, small);
+  const int64_t spans = span_count(nnz);
+  // spans a block takes at a time: as many as fit in LDS beside the buckets' words, but few
+  // where that left CUs without a block (creation at m = 3e5 with 16 / 64: 68 / 79 us)
+  const int take = buckets > kFewBuckets ? 32 : spans >= 64 * 256 ? 64 : 16;
+  const int grid = (int)std::min<int64_t>((spans + take - 1) / take, kCheckBlocks);
+  auto* kernel = take == 64   ? k_edge_bucket<64, kFewBuckets>
+                 : take == 32 ? k_edge_bucket<32, 1u << kMaxBucketBits>
+                              : k_edge_bucket<16, kFewBuckets>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBucketThreads), buckets * sizeof(uint32_t), s, nnz, span_row, n, rp, col,
+                     full ? 1 : 0, slots, hash_bits, fill, part, small);
   hipLaunchKernelGGL(k_bucket_build, dim3(buckets), dim3(kBucketThreads), 0, s, slots, hash_bits, filter, filter_bits,
                      fill, spill, spill_cap, fill + buckets, part, grid, small);
   hipLaunchKernelGGL(k_bucket_spill, dim3(8), dim3(256), 0, s, (unsigned long long*)slots, hash_bits, spill, spill_cap,
