@@ -139,7 +139,7 @@ hipError_t launch_edge_insert(int64_t nnz, const int32_t* span_row, const int32_
 // edge_bucket_count + 1 words, zeroed beforehand; `spill`: spill_cap words.  Neither the
 // slots nor the filter need clearing.  small[kWBucketFull] is set when some bucket or the
 // list did not hold its keys; the set is then built by launch_edge_insert instead.
-constexpr int64_t kBucketMinEdges = 1 << 17;
+constexpr int64_t kBucketMinEdges = 1 << 15;
 constexpr int kMaxBucketBits = 14;
 constexpr uint32_t kSpillCap = 1u << 16;
 bool edge_set_by_buckets(int64_t m, int hash_bits);

@@ -631,9 +631,9 @@ hipError_t launch_check_items(int64_t nnz, const int32_t* span_row, int32_t n, c
 // (or the spill list) raises kWBucketFull and the host builds the graph again by
 // k_edge_insert, which holds for keys of any distribution.
 // Against fills of the table, k_edge_insert, k_filter_build and k_check_items (random
-// compare-and-swaps at 2e10 and lookups at 4e10 a second), creation at m = 2e5 / 1e6 / 3e6 /
-// 1e7 89 / 148 / 311 / 905 -> 71 / 86 / 131 / 330 us; at
-// m = 1e5 no difference.
+// compare-and-swaps at 2e10 and lookups at 4e10 a second), creation at m = 5e4 / 1e5 /
+// 2e5 / 1e6 / 3e6 / 1e7 77 / 81 / 89 / 148 / 311 / 905 -> 70 / 71 / 71 / 86 / 131 / 330 us;
+// at m = 3e4 no difference.
 constexpr int kBucketBits = 13;
 constexpr uint32_t kBucket = 1u << kBucketBits;
 constexpr int kBucketThreads = 1024;

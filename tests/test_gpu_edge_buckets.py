@@ -1,4 +1,4 @@
-"""Creation by buckets (graphs of at least 2^17 edges): every defect is reported as by the
+"""Creation by buckets (graphs of at least 2^15 edges): every defect is reported as by the
 general way, a set whose keys crowd into one bucket is built the general way, and probes
 against either set give the oracle's classes."""
 import numpy as np
@@ -86,6 +86,20 @@ def test_keys_in_one_bucket():
     g, og = _create(csr.row_ptr, csr.col), oracle.Graph(csr)
     s = moss.MOSS_SAMPLER_T5
     np.testing.assert_array_equal(g.sample_range(s, 4, 0, 50_000), og.run(ORACLE_SAMPLER[s], 4, 0, 50_000, 8))
+    c = csr.col.copy()
+    c[0] = (set(range(1, int(c[1]))) - {int(c[0])}).pop()
+    with pytest.raises(moss.MossError) as x:
+        _create(csr.row_ptr, c)
+    assert x.value.status == moss.MOSS_E_ASYMMETRIC
+
+
+@pytest.mark.parametrize("m", [(1 << 15) - 1, 1 << 15, (1 << 15) + 1, 50_003])
+def test_around_the_smallest(m):
+    """From 2^15 edges on the set is built by buckets (16 of them there)."""
+    csr = gg.from_edges(9_000, _edges(9_000, m, m), "gnm")
+    g, og = _create(csr.row_ptr, csr.col), oracle.Graph(csr)
+    for s in (moss.MOSS_SAMPLER_MOSS4, moss.MOSS_SAMPLER_T5):
+        np.testing.assert_array_equal(g.sample_range(s, 3, 0, 20_000), og.run(ORACLE_SAMPLER[s], 3, 0, 20_000, 8))
     c = csr.col.copy()
     c[0] = (set(range(1, int(c[1]))) - {int(c[0])}).pop()
     with pytest.raises(moss.MossError) as x:
