@@ -3,8 +3,10 @@
 // Graph creation (Section 2: an undirected simple graph as sorted CSR):
 //   k_node_prep        row_ptr checks, largest degree, work-item and row-guide sizes
 //   k_items_records    work items (rows cut into pieces), node records, span rows
-//   k_edge_insert      the edge hash set (then k_filter_build: the edge filter)
-//   k_check_items      column range, self-loops, strict ascent, symmetry
+//   k_edge_bucket      column range, self-loops, strict ascent; the edges' keys by buckets
+//   k_bucket_build     each bucket's part of the edge hash set and filter; symmetry
+//   k_edge_insert, k_filter_build, k_check_items   the same by random accesses: small
+//                      graphs, and keys that crowd into few buckets
 // Table build (Section 4.1.3 "Initialization", O(|E|)):
 //   k_span_prefix      each 256-entry span's prefix of ACC_sigma, ACC_tau or the
 //                      MOSS-4Min row weights, restarted at every row start
@@ -14,8 +16,10 @@
 //   k_scan_*           node-level inclusive prefixes ACC_Gamma*
 //   k_guides           search windows for the node draws
 // Sampling (Algorithms 1, 3, 4):
-//   k_sample<S>        grid-stride loop, one sample per lane per step,
-//                      per-wave LDS histograms flushed with u64 atomics
+//   k_sample<S0, S1>   one or two samplers a launch, chunks of samples in lane order,
+//                      per-wave LDS histograms; the last block hands the counts over
+//   k_sort_*, k_sample_sorted<S>   the same by groups of nodes, for many samples of
+//                      large graphs
 //   k_batch            persistent kernel cutting a list of many
 //                      (graph, sampler, sample range) items into tiles
 //   k_sample_nodes<S>  the same draw for chosen sample indices, with nodes
