@@ -81,6 +81,14 @@ struct BatchItem {
 // samples per tile.
 constexpr int kCtlTiles = 0, kCtlCounter = 1, kCtlItems = 2, kCtlTileSize = 3;
 
+// The tile of a block whose claim took `claimed` from the counter: every block draws the
+// tile of its own number first, so claims begin at the grid's size.  `tiles` (more than the
+// grid) once the list is drained: the blocks' last, failed claims go up to the number of
+// tiles, and counted on from the grid they would pass 2^32 where the list nearly fills it.
+__host__ __device__ constexpr uint32_t next_tile(uint32_t claimed, uint32_t grid, uint32_t tiles) {
+  return claimed < tiles - grid ? grid + claimed : tiles;
+}
+
 hipError_t upload_class_luts(const uint8_t lut4[8], const uint8_t lut5t[64], const uint8_t lut5p[64]);
 
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t count, hipStream_t s);

@@ -3514,7 +3514,7 @@ __global__ __launch_bounds__(256, kSampleWaves) void k_batch(const SamplerView* 
       if (s) atomicAdd(&bins[(uint64_t)it.out * kBins + tid], (unsigned long long)s);
     }
     if (n_tiles <= gridDim.x) break;  // every tile has had its block
-    if (tid == 0) cur = gridDim.x + atomicAdd(&ctl[kCtlCounter], 1u);
+    if (tid == 0) cur = next_tile(atomicAdd(&ctl[kCtlCounter], 1u), gridDim.x, n_tiles);
     __syncthreads();
     t = __builtin_amdgcn_readfirstlane(cur);
   }
