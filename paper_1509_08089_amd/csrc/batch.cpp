@@ -313,7 +313,6 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
   const size_t items_at = pad(views.size() * sizeof(SamplerView));
   const size_t ctl_at = items_at + pad(items.size() * sizeof(BatchItem)), bytes = ctl_at + pad(4 * sizeof(uint32_t));
   const uint64_t words = (uint64_t)n_slots * 22;
-  if (words > 0xFFFFFFFFull) return MOSS_E_ARG;
   moss_status st = reserve(bytes, n_slots);
   if (st != MOSS_OK) return st;
   std::memcpy(h_in_, views.data(), views.size() * sizeof(SamplerView));
@@ -333,7 +332,7 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
     e = hipEventRecord(ev_wait_, wait_on);
     if (e == hipSuccess) e = hipStreamWaitEvent(stream_, ev_wait_, 0);
   }
-  if (e == hipSuccess) e = launch_batch_stage(h_in_, d_in_, bytes, d_bins_, (uint32_t)words, d_end_, stream_);
+  if (e == hipSuccess) e = launch_batch_stage(h_in_, d_in_, bytes, d_bins_, words, d_end_, stream_);
   // the grouped launches run on the side streams, beside the persistent kernel (whose
   // latency-bound waves leave block slots and memory bandwidth free), from the clear on;
   // each chunk goes to the chain with less cost so far.  Two chains measured 1%
@@ -362,7 +361,7 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
     e = hipEventRecord(ev_side_[j], side_[j]);
     if (e == hipSuccess) e = hipStreamWaitEvent(stream_, ev_side_[j], 0);
   }
-  if (e == hipSuccess) e = launch_batch_collect(d_bins_, (uint32_t)words, d_end_, host, seq, stream_);
+  if (e == hipSuccess) e = launch_batch_collect(d_bins_, words, d_end_, host, seq, stream_);
   // the slots are in host memory once the sequence number is
   bool there = false;
   if (e == hipSuccess) {

@@ -343,11 +343,11 @@ hipError_t launch_sample_nodes(int sampler, const SamplerView& v, uint64_t seed,
 // host[kBatchHostWords ..), the device ticks since the stage and then `seq`).  `end`: two
 // device words of theirs.
 constexpr int kBatchHostSeq = 0, kBatchHostTicks = 1, kBatchHostWords = 2;
-hipError_t launch_batch_stage(const void* host, void* dev, size_t bytes, unsigned long long* bins, uint32_t words,
+hipError_t launch_batch_stage(const void* host, void* dev, size_t bytes, unsigned long long* bins, uint64_t words,
                               unsigned long long* end, hipStream_t s);
 hipError_t launch_batch(const SamplerView* views, const BatchItem* items, uint32_t* ctl, unsigned long long* bins,
                         int grid, int block, hipStream_t s);
-hipError_t launch_batch_collect(const unsigned long long* bins, uint32_t words, unsigned long long* end,
+hipError_t launch_batch_collect(const unsigned long long* bins, uint64_t words, unsigned long long* end,
                                 unsigned long long* host, uint64_t seq, hipStream_t s);
 
 // Registers/VGPR usage probe for occupancy decisions (max active blocks per CU).

@@ -3438,22 +3438,22 @@ hipError_t launch_sample_nodes(int sampler, const SamplerView& v, uint64_t seed,
 // the events around the batch 6 us.
 // ---------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_batch_stage(const uint4* __restrict__ host, uint4* __restrict__ dev,
-                                                     uint32_t quads, unsigned long long* __restrict__ bins,
-                                                     uint32_t words, unsigned long long* __restrict__ end) {
+                                                     uint64_t quads, unsigned long long* __restrict__ bins,
+                                                     uint64_t words, unsigned long long* __restrict__ end) {
   const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
-  for (uint32_t i = i0; i < quads; i += step) dev[i] = host[i];
-  for (uint32_t i = i0; i < words; i += step) bins[i] = 0;
+  for (uint64_t i = i0; i < quads; i += step) dev[i] = host[i];
+  for (uint64_t i = i0; i < words; i += step) bins[i] = 0;
   if (i0 == 0) {
     end[0] = 0;  // blocks of k_batch_collect that are done
     end[1] = (unsigned long long)wall_clock64();
   }
 }
 
-__global__ __launch_bounds__(256) void k_batch_collect(const unsigned long long* __restrict__ bins, uint32_t words,
+__global__ __launch_bounds__(256) void k_batch_collect(const unsigned long long* __restrict__ bins, uint64_t words,
                                                        unsigned long long* __restrict__ end,
                                                        unsigned long long* __restrict__ host, uint64_t seq) {
   __shared__ uint32_t last;
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x)
+  for (uint64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x)
     host[kBatchHostWords + i] = bins[i];
   __threadfence_system();
   __syncthreads();
@@ -3520,10 +3520,10 @@ __global__ __launch_bounds__(256, kSampleWaves) void k_batch(const SamplerView* 
   }
 }
 
-hipError_t launch_batch_stage(const void* host, void* dev, size_t bytes, unsigned long long* bins, uint32_t words,
+hipError_t launch_batch_stage(const void* host, void* dev, size_t bytes, unsigned long long* bins, uint64_t words,
                               unsigned long long* end, hipStream_t s) {
-  const uint32_t quads = (uint32_t)(bytes / 16);
-  if (bytes % 16 || bytes / 16 > 0xFFFFFFFFull) return hipErrorInvalidValue;
+  const uint64_t quads = bytes / 16;
+  if (bytes % 16) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_batch_stage, dim3((unsigned)std::max(1, std::min(fill_grid(std::max(quads, words)), 256))),
                      dim3(256), 0, s, static_cast<const uint4*>(host), static_cast<uint4*>(dev), quads, bins, words, end);
   return hipGetLastError();
@@ -3536,7 +3536,7 @@ hipError_t launch_batch(const SamplerView* views, const BatchItem* items, uint32
   return hipGetLastError();
 }
 
-hipError_t launch_batch_collect(const unsigned long long* bins, uint32_t words, unsigned long long* end,
+hipError_t launch_batch_collect(const unsigned long long* bins, uint64_t words, unsigned long long* end,
                                 unsigned long long* host, uint64_t seq, hipStream_t s) {
   hipLaunchKernelGGL(k_batch_collect, dim3((unsigned)std::max(1, std::min(fill_grid(words), 64))), dim3(256), 0, s,
                      bins, words, end, host, seq);

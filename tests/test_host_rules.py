@@ -1,19 +1,35 @@
 """Rules of the host code, on the CPU: small programs compiled against the library's own
-headers."""
+headers and, where they call it, linked with a stand-in for the HIP runtime (fake_hip.c)."""
 import os
 import subprocess
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1509_08089_amd", "csrc")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+LIB = os.path.join(ROOT, "paper_1509_08089_amd", "libmoss.so")
 
 
-def _run(tmp_path, source, *link):
+@pytest.fixture(scope="module")
+def fake_hip(tmp_path_factory):
+    """Folder of the stand-in, under the runtime's name."""
+    where = tmp_path_factory.mktemp("hip")
+    subprocess.check_call(["gcc", "-shared", "-fPIC", "-w", "-Wl,-soname,libamdhip64.so.7",
+                           os.path.join(ROOT, "tests", "fake_hip.c"), "-o", str(where / "libamdhip64.so.7")])
+    return str(where)
+
+
+def _run(tmp_path, source, hip=None):
+    """The output of a program, linked with the library on the stand-in in folder `hip`."""
     src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    link = [LIB, os.path.join(hip, "libamdhip64.so.7"), "-Wl,-rpath," + os.path.dirname(LIB),
+            "-Wl,--unresolved-symbols=ignore-in-shared-libs"] if hip else []  # the stand-in's symbols have no version
     src.write_text(source)
     subprocess.check_call(["g++", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
                            "-I", CSRC, "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe), *link])
-    return subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
+    env = {**os.environ, "LD_LIBRARY_PATH": hip} if hip else None
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True, env=env).stdout
 
 
 def test_tiles_of_claims(tmp_path):
@@ -40,3 +56,18 @@ int main() {
 }
 """)
     assert out == "ok\n"
+
+
+@pytest.mark.parametrize("words", [22, 2**32 - 1, 2**32 + 5, 22 * (2**32 - 1)])
+def test_histogram_words_of_a_batch(tmp_path, fake_hip, words):
+    """A batch has 22 words a slot and as many slots as memory holds: the kernels that clear
+    and collect them count beyond 32 bits."""
+    out = _run(tmp_path, """
+#include "kernels.h"
+int main() {
+  const uint64_t words = %dull;
+  if (moss::launch_batch_stage(nullptr, nullptr, 64, nullptr, words, nullptr, nullptr) != hipSuccess) return 1;
+  if (moss::launch_batch_collect(nullptr, words, nullptr, nullptr, 1, nullptr) != hipSuccess) return 2;
+}
+""" % words, fake_hip)
+    assert [x for x in out.splitlines() if x.startswith("words")] == ["words %d" % words] * 2
