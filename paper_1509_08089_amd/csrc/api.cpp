@@ -406,7 +406,8 @@ NodeLayout node_layout(const moss_graph* g, bool k5) {
   return L;
 }
 
-// Small pinned host buffers for results and flags, reused across graphs.
+// Small pinned host buffers for results and flags, reused across graphs.  A slab serves
+// graphs of any device, whose kernels store counts into it, so it is allocated for all.
 std::mutex g_pin_mu;
 std::vector<uint64_t*> g_pin_free;
 constexpr size_t kPinWords = kWords;
@@ -415,7 +416,7 @@ uint64_t* pinned_chunk() {
   std::lock_guard<std::mutex> lk(g_pin_mu);
   if (g_pin_free.empty()) {
     uint64_t* slab = nullptr;
-    if (hipHostMalloc((void**)&slab, 64 * kPinWords * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess)
+    if (hipHostMalloc((void**)&slab, 64 * kPinWords * sizeof(uint64_t), hipHostMallocPortable) != hipSuccess)
       return nullptr;
     for (int i = 0; i < 64; ++i) g_pin_free.push_back(slab + i * kPinWords);
   }

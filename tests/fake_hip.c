@@ -18,7 +18,7 @@ int hipDeviceGetAttribute(int* v, int what, int d) { *v = 256; return 0; }
 int hipDeviceGetDefaultMemPool(void** p, int d) { *p = NULL; return 0; }
 int hipMemPoolSetAttribute(void* p, int what, void* v) { return 0; }
 int hipGetLastError(void) { return 0; }
-int hipGetSymbolAddress(void** p, const void* symbol) { *p = NULL; return 1; }
+int hipGetSymbolAddress(void** p, const void* symbol) { *p = (void*)symbol; return 0; }
 int hipMemcpyToSymbol(const void* symbol, const void* from, size_t size, size_t at, int kind) { return 0; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void* f, int block, size_t lds) { *n = 7; return 0; }
 

@@ -71,3 +71,45 @@ int main() {
 }
 """ % words, fake_hip)
     assert [x for x in out.splitlines() if x.startswith("words")] == ["words %d" % words] * 2
+
+
+PATH_GRAPH = """
+#include <vector>
+#include "hip/hip_runtime.h"
+#include "moss.h"
+// a path of m edges, made on a device; kernels don't run here, so checked graphs end refused
+static moss_status make(int device, int m, uint32_t flags, moss_graph** g) {
+  std::vector<int32_t> rp(m + 2), col;
+  for (int v = 0; v <= m; ++v) {
+    if (v > 0) col.push_back(v - 1);
+    if (v < m) col.push_back(v + 1);
+    rp[v + 1] = (int32_t)col.size();
+  }
+  hipSetDevice(device);
+  return moss_graph_create(m + 1, (int64_t)col.size(), rp.data(), col.data(), flags, nullptr, g);
+}
+"""
+
+
+def test_pinned_words_of_two_devices(tmp_path, fake_hip):
+    """The pinned words that a graph's kernels store into belong to its device or to all,
+    also where a graph of another device had them before."""
+    out = _run(tmp_path, PATH_GRAPH + """
+int main() {
+  for (int device : {0, 1}) {
+    moss_graph* g = nullptr;
+    if (make(device, 100, MOSS_TRUST_CSR, &g) != MOSS_OK || moss_graph_destroy(g) != MOSS_OK) return 1;
+  }
+}
+""", fake_hip)
+    blocks, used = [], set()
+    for f in map(str.split, out.splitlines()):
+        if f[:2] == ["host", "block"]:
+            at = int(f[4], 16)
+            blocks.append((at, at + int(f[5]), int(f[2]), int(f[3])))
+        elif f[0] == "copy" and f[2] == "2":  # to the host
+            device, to = int(f[1]), int(f[3], 16)
+            (owner, flags), = [b[2:] for b in blocks if b[0] <= to < b[1]]
+            used.add(device)
+            assert owner == device or flags & 1, (owner, device, flags)  # 1: hipHostMallocPortable
+    assert used == {0, 1}
