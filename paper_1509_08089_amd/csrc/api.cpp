@@ -320,11 +320,12 @@ T* at(void* base, size_t off) {
 // per graph: word block, edge hash set and filter, items, item sums, row-guide lengths,
 // scan scratch, partials, records
 struct GraphLayout {
-  size_t small, hit_parts, slots, filter, items, item_sum, guide_len, tmp[3], partials, rec, span_row, check_part, span_sums,
-      span_groups, group_wrap, hub_filter, bucket_fill, spill, bytes;
+  size_t small, hit_parts, slots, filter, items, item_sum, guide_len, tmp[3], partials, rec, span_row, check_part,
+      span_sums, span_groups, group_wrap, hub_filter, bucket_fill, spill, bytes;
+  uint32_t spill_cap;
 };
 
-GraphLayout graph_layout(int32_t n, int64_t nnz) {
+GraphLayout graph_layout(int32_t n, int64_t nnz, uint32_t flags) {
   const int64_t cap = items_cap(n, nnz);
   GraphLayout L;
   Carve c;
@@ -343,10 +344,12 @@ GraphLayout graph_layout(int32_t n, int64_t nnz) {
   L.span_sums = c.take<uint64_t>(2 * (size_t)std::max<int64_t>(1, span_count(nnz)));
   L.span_groups = c.take<uint64_t>((size_t)std::max<int64_t>(1, span_group_count(nnz)));
   L.group_wrap = c.take<uint32_t>((size_t)std::max<int64_t>(1, span_group_count(nnz)));
-  L.hub_filter = c.take<uint8_t>((size_t)nnz);
+  // a byte an entry where the graph may have hub filters (the largest degree is not known yet)
+  L.hub_filter = c.take<uint8_t>(hub_filters_possible(flags, edge_filter_bits(nnz / 2)) ? (size_t)nnz : 0);
   const bool buckets = edge_set_by_buckets(nnz / 2, edge_hash_bits(nnz / 2));
   L.bucket_fill = c.take<uint32_t>(buckets ? (size_t)edge_bucket_count(edge_hash_bits(nnz / 2)) + 1 : 0);
-  L.spill = c.take<uint64_t>(buckets ? kSpillCap : 0);
+  L.spill_cap = buckets ? spill_capacity(edge_hash_bits(nnz / 2)) : 0;
+  L.spill = c.take<uint64_t>(L.spill_cap);
   L.bytes = c.off;
   return L;
 }
@@ -493,7 +496,7 @@ int validate_error_status(uint32_t bits) {
 // records, the edge hash set and filter, the column and symmetry checks, one copy
 // back and one synchronisation.
 moss_status finish_create(moss_graph* g) {
-  const GraphLayout L = graph_layout(g->n, g->nnz);
+  const GraphLayout L = graph_layout(g->n, g->nnz, g->flags);
   moss_status st = dev_alloc_bytes(g->stream, &g->mem_graph, L.bytes);
   if (st != MOSS_OK) return st;
   void* m = g->mem_graph;
@@ -572,7 +575,7 @@ moss_status finish_create(moss_graph* g) {
                              g->small, s);
   if (e == hipSuccess)
     e = buckets ? launch_edge_buckets(g->nnz, g->span_row, g->n, g->rp, g->col, full, g->edge_slots, g->edge_bits,
-                                      g->filter, g->filter_bits, bucket_fill, at<uint64_t>(m, L.spill), kSpillCap,
+                                      g->filter, g->filter_bits, bucket_fill, at<uint64_t>(m, L.spill), L.spill_cap,
                                       g->check_part, g->small, s)
                 : edge_set_by_swaps();
   if (e == hipSuccess) e = copy_back();

@@ -44,7 +44,7 @@ struct moss_graph {
   uint64_t* span_sums = nullptr;         // 2 per span: the row-prefix passes' span sums
   uint64_t* span_groups = nullptr;       // per 64 spans: their summed span sums
   uint32_t* group_wrap = nullptr;        // per 64 spans: whether that sum wrapped
-  uint64_t* hub_filter = nullptr;        // nnz bytes: hub rows' own filters
+  uint64_t* hub_filter = nullptr;        // hub rows' own filters: nnz bytes, none where hub_filters_possible fails
   int64_t n_items = 0;
   int64_t row_guide_len = 0;             // entries of one row-guide array
 
@@ -79,9 +79,14 @@ struct moss_graph {
 
 namespace moss {
 
-// whether g's hub rows have filters of their own
+// whether hub rows have filters of their own, in a graph that has hubs
+inline bool hub_filters_possible(uint32_t flags, int filter_bits) {
+  return !(flags & MOSS_TRUST_CSR) && filter_bits >= kHubMinFilterBits;
+}
+
+// whether g's hub rows have them
 inline bool has_hub_filters(const moss_graph* g) {
-  return !(g->flags & MOSS_TRUST_CSR) && g->max_degree >= kHubMinDegree && g->filter_bits >= kHubMinFilterBits;
+  return hub_filters_possible(g->flags, g->filter_bits) && g->max_degree >= kHubMinDegree;
 }
 
 // index of a sampler's node distribution / tables

@@ -152,6 +152,8 @@ constexpr int kMaxBucketBits = 14;
 constexpr uint32_t kSpillCap = 1u << 16;
 bool edge_set_by_buckets(int64_t m, int hash_bits);
 int64_t edge_bucket_count(int hash_bits);
+// Words of the spill list: what the buckets can spill together, at most kSpillCap.
+uint32_t spill_capacity(int hash_bits);
 hipError_t launch_edge_buckets(int64_t nnz, const int32_t* span_row, int32_t n, const int32_t* rp, const int32_t* col,
                                bool full, uint64_t* slots, int hash_bits, uint64_t* filter, int filter_bits,
                                uint32_t* fill, uint64_t* spill, uint32_t spill_cap, uint64_t* part, uint64_t* small,

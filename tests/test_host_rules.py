@@ -74,6 +74,8 @@ int main() {
 
 
 PATH_GRAPH = """
+#include <sys/wait.h>
+#include <unistd.h>
 #include <vector>
 #include "hip/hip_runtime.h"
 #include "moss.h"
@@ -113,3 +115,30 @@ int main() {
             used.add(device)
             assert owner == device or flags & 1, (owner, device, flags)  # 1: hipHostMallocPortable
     assert used == {0, 1}
+
+
+def test_memory_of_a_graph(tmp_path, fake_hip):
+    """The hub filters' bytes are held where a graph may have them: a checked one of more
+    than 2^19 edges.  The bucketed creation's list grows with its buckets."""
+    out = _run(tmp_path, PATH_GRAPH + """
+int main() {
+  for (uint32_t flags : {0u, MOSS_TRUST_CSR})
+    for (int m : {(1 << 15) - 8, 1 << 15, 1 << 19, (1 << 19) + 8}) {
+      if (fork() == 0) {  // a process each: the library keeps released blocks for the next graph
+        moss_graph* g = nullptr;
+        (void)make(0, m, flags, &g);
+        return 0;
+      }
+      wait(nullptr);
+    }
+}
+""", fake_hip)
+    size = [int(x.split()[3]) for x in out.splitlines() if x.startswith("device block")]
+    per_graph = size[1::2]  # a graph's CSR, then its own block
+    assert len(size) == 16
+    checked, trusted = per_graph[:4], per_graph[4:]
+    grain = 2 << 20  # of blocks past 8 MB (64 KB below)
+    assert checked[:3] == trusted[:3]
+    assert checked[3] - trusted[3] >= 2 * (1 << 19) - grain and checked[3] > trusted[3]
+    assert trusted[3] - trusted[2] <= (1 << 19) + grain  # the filter doubles there: half a MB
+    assert checked[1] - checked[0] <= 2 * (64 << 10)
