@@ -867,6 +867,11 @@ moss_status moss::build_tables(moss_graph* g, uint32_t k_mask) {
   f.count[0] = kWLambda + 2;
   f.p[1] = g->small + kWTotal;
   f.count[1] = 4;
+  const bool hub_filters = want_sig && has_hub_filters(g);
+  if (hub_filters && hub_rows_to_clear(g->max_degree)) {
+    f.p[2] = g->hub_filter;
+    f.count[2] = g->nnz / 8;  // the filters are whole words within nnz bytes
+  }
   hipError_t e = launch_fill_set(f, s);
   RowTables t{};
   t.rp = g->rp;
@@ -881,7 +886,7 @@ moss_status moss::build_tables(moss_graph* g, uint32_t k_mask) {
   t.rec = g->rec;
   t.nnz = g->nnz;
   t.n = g->n;
-  if (e == hipSuccess && want_sig && has_hub_filters(g))
+  if (e == hipSuccess && hub_filters)
     e = launch_hub_filter(g->nnz, g->span_row, g->rec, g->col, g->hub_filter, s);
   if (e == hipSuccess && want_sig) {
     t.guide = g->sig_guide;

@@ -237,6 +237,10 @@ int edge_filter_bits(int64_t m);
 // without.
 constexpr int32_t kHubMinDegree = 256;
 constexpr int kHubMinFilterBits = 17;
+constexpr uint32_t kHubBlockWords = 2048;
+// Whether some row's filter may have more words than kHubBlockWords (a row of d entries has
+// at most d / 64 units of eight): launch_hub_filter then expects the hub filters cleared.
+bool hub_rows_to_clear(int32_t max_degree);
 hipError_t launch_hub_filter(int64_t nnz, const int32_t* span_row, const uint4* rec, const int32_t* col, uint64_t* hub,
                              hipStream_t s);
 

@@ -429,14 +429,19 @@ __global__ __launch_bounds__(256) void k_filter_build(const uint64_t* __restrict
 // it there: the windows and chunks in lane order share v, so those reads stay in the L1
 // and L2 and only the pairs without a hub go to the large filter.
 // A hub holds the first entry of some span (kHubMinDegree >= kSpan), and the first such
-// span finds it.  A block puts a hub's filter together in LDS, kSeg words at a time.
+// span finds it.  A block puts the filter of a hub of up to kHubBlockWords words (some
+// 16,384 entries) together in LDS, in one pass over the row.  Longer rows, cleared
+// beforehand (hub_rows_to_clear), are filled span by span by all the blocks that their
+// spans fall to, a wave a span, with atomics: a block's passes over such a row, one for
+// every kHubBlockWords words, took 54 ms for a row of 2^20 entries, where all other passes
+// of a table build take 0.16.
 __global__ __launch_bounds__(256) void k_hub_filter(int64_t nnz, const int32_t* __restrict__ span_row,
                                                     const uint4* __restrict__ rec, const int32_t* __restrict__ col,
                                                     uint2* __restrict__ hub) {
-  constexpr uint32_t kSeg = 2048;
-  __shared__ uint32_t bits[2 * kSeg];
-  __shared__ int32_t list[64];
-  __shared__ uint32_t found;
+  __shared__ uint32_t bits[2 * kHubBlockWords];
+  __shared__ int32_t list[64];                // hubs that a block puts together
+  __shared__ uint8_t shared_spans[64];        // spans of longer rows
+  __shared__ uint32_t found, shared_found;
   const int tid = threadIdx.x;
   const int64_t spans = (nnz + kSpan - 1) / kSpan;
   for (int64_t s0 = (int64_t)blockIdx.x * 64; s0 < spans; s0 += (int64_t)gridDim.x * 64) {
@@ -444,37 +449,53 @@ __global__ __launch_bounds__(256) void k_hub_filter(int64_t nnz, const int32_t* 
       const int64_t sp = s0 + tid;
       const int32_t v = sp < spans ? span_row[sp] : 0;
       const bool first = sp < spans && (sp == 0 || span_row[sp - 1] != v);
-      const bool is = first && row_of(rec, v).y >= (uint32_t)kHubMinDegree;
-      const uint64_t all = __ballot(is);
-      if (is) list[__popcll(all & ((1ull << tid) - 1))] = v;
-      if (tid == 0) found = (uint32_t)__popcll(all);
+      const uint2 R = row_of(rec, v);
+      const bool is = sp < spans && R.y >= (uint32_t)kHubMinDegree, more = is && hub_words(R.x, R.y) > kHubBlockWords;
+      const uint64_t all = __ballot(is && first && !more), spread = __ballot(more);
+      if (is && first && !more) list[__popcll(all & ((1ull << tid) - 1))] = v;
+      if (more) shared_spans[__popcll(spread & ((1ull << tid) - 1))] = (uint8_t)tid;
+      if (tid == 0) {
+        found = (uint32_t)__popcll(all);
+        shared_found = (uint32_t)__popcll(spread);
+      }
     }
     __syncthreads();
-    const uint32_t hubs = found;
+    const uint32_t hubs = found, pieces = shared_found;
     for (uint32_t i = 0; i < hubs; ++i) {
       const int32_t v = list[i];
       const uint2 R = row_of(rec, v);
       const uint32_t first = hub_first(R.x), words = hub_words(R.x, R.y);
-      for (uint32_t w0 = 0; w0 < words; w0 += kSeg) {
-        const uint32_t len = min(kSeg, words - w0);
-        for (uint32_t j = tid; j < 2 * len; j += 256) bits[j] = 0;
-        __syncthreads();
-        for (uint32_t j = tid; j < R.y; j += 256) {
-          const EdgeHash h = edge_hash(edge_key(v, col[(int64_t)R.x + j]));
-          const uint32_t w = hub_word(R.x, R.y, h) - first - w0;
-          if (w >= len) continue;
-          const uint2 m = filter_mask(h);
-          atomicOr(&bits[2 * w], m.x);
-          atomicOr(&bits[2 * w + 1], m.y);
-        }
-        __syncthreads();
-        for (uint32_t j = tid; j < len; j += 256) hub[(size_t)first + w0 + j] = make_uint2(bits[2 * j], bits[2 * j + 1]);
-        __syncthreads();
+      for (uint32_t j = tid; j < 2 * words; j += 256) bits[j] = 0;
+      __syncthreads();
+      for (uint32_t j = tid; j < R.y; j += 256) {
+        const EdgeHash h = edge_hash(edge_key(v, col[(int64_t)R.x + j]));
+        const uint32_t w = hub_word(R.x, R.y, h) - first;
+        const uint2 m = filter_mask(h);
+        atomicOr(&bits[2 * w], m.x);
+        atomicOr(&bits[2 * w + 1], m.y);
+      }
+      __syncthreads();
+      for (uint32_t j = tid; j < words; j += 256) hub[(size_t)first + j] = make_uint2(bits[2 * j], bits[2 * j + 1]);
+      __syncthreads();
+    }
+    for (uint32_t i = tid >> 6; i < pieces; i += 4) {  // wave-uniform
+      const int64_t sp = s0 + shared_spans[i], S = sp * kSpan;
+      const int32_t v = span_row[sp];
+      const uint2 R = row_of(rec, v);
+      // the row's first such span also takes the entries before it, fewer than kSpan
+      const int64_t from = S - R.x < kSpan ? (int64_t)R.x : S, to = min((int64_t)R.x + R.y, S + kSpan);
+      for (int64_t e = from + lane_id(); e < to; e += 64) {
+        const EdgeHash h = edge_hash(edge_key(v, col[e]));
+        const uint2 m = filter_mask(h);
+        atomicOr(reinterpret_cast<unsigned long long*>(hub) + hub_word(R.x, R.y, h),
+                 (unsigned long long)m.y << 32 | m.x);
       }
     }
-    __syncthreads();  // the list is written again
+    __syncthreads();  // the lists are written again
   }
 }
+
+bool hub_rows_to_clear(int32_t max_degree) { return (uint32_t)max_degree / 64 * 8 > kHubBlockWords; }
 
 hipError_t launch_hub_filter(int64_t nnz, const int32_t* span_row, const uint4* rec, const int32_t* col, uint64_t* hub,
                              hipStream_t s) {
