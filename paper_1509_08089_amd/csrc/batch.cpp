@@ -179,10 +179,9 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
   std::map<std::pair<const moss_graph*, int>, uint32_t> view_of;
   std::vector<BatchItem> items;
   std::vector<uint64_t> item_cost;
-  // large items on large graphs run as grouped launches of their own after the
-  // persistent kernel (the plain path's grouping passes and sorted sampling kernel, in
-  // two chains of chunks, each chain one chunk at a time through a scratch block of its
-  // own), adding into their histogram slots
+  // large items on large graphs run as grouped launches of their own (the plain path's
+  // grouping passes and sorted sampling kernel, in two chains of chunks, each chain one
+  // chunk at a time through a scratch block of its own), adding into their histogram slots
   struct SortChunk {
     int sampler;
     uint64_t seed, a, n;
@@ -269,10 +268,9 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
   // moment the chip works on one graph's tables and they stay in L2 and the MALL
   // (interleaving the graphs of a batch measured about 15% slower per sample).  The
   // views of the graphs with the largest sampled footprint go first, then those with
-  // the most work, and the largest items first within a view: the large graphs' items
-  // then run while the grouped launches on the side stream read the same tables (0.8%
-  // faster on a 256-request batch than most work first; smallest graphs first was 1%
-  // slower).  The kernel cuts each item into tiles itself; the host hands over the
+  // the most work, and the largest items first within a view (256 requests over 32
+  // graphs: largest footprint / most work / smallest footprint first 18.84 / 18.72 / 18.80
+  // ms, no more apart than the runs of one).  The kernel cuts each item into tiles itself; the host hands over the
   // item list only.
   std::vector<uint64_t> view_cost(views.size(), 0), view_fp(views.size(), 0);
   for (size_t i = 0; i < items.size(); ++i) view_cost[items[i].view] += item_cost[i];
@@ -333,11 +331,12 @@ moss_status BatchRunner::run(const std::vector<WorkItem>& work, uint32_t n_slots
     if (e == hipSuccess) e = hipStreamWaitEvent(stream_, ev_wait_, 0);
   }
   if (e == hipSuccess) e = launch_batch_stage(h_in_, d_in_, bytes, d_bins_, words, d_end_, stream_);
-  // the grouped launches run on the side streams, beside the persistent kernel (whose
-  // latency-bound waves leave block slots and memory bandwidth free), from the clear on;
-  // each chunk goes to the chain with less cost so far.  Two chains measured 1%
-  // faster than one on a 256-request batch: one chain's passes had outlasted the
-  // persistent kernel by 2.5 ms.
+  // the grouped launches go to the side streams, free to start from the clear on.  They do
+  // not run beside the persistent kernel, though: their first pass has blocks of 1024
+  // threads, four wave places on every SIMD of a CU, of which the persistent kernel holds
+  // six of eight until its list is drained.  So the two chains follow it and overlap one
+  // another only; each chunk goes to the chain with less cost so far.  With one chain 256
+  // requests over 32 graphs take 20.6 ms instead of 18.8, 40 over 6 7.45 instead of 6.32.
   const int side = chunks.empty() ? 0 : chains;
   if (e == hipSuccess && side) e = hipEventRecord(ev_clear_, stream_);
   for (int j = 0; j < side && e == hipSuccess; ++j) e = hipStreamWaitEvent(side_[j], ev_clear_, 0);

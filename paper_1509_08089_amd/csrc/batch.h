@@ -30,14 +30,14 @@ class BatchRunner {
   // first.  tile_samples / blocks_per_cu of 0 use the current tuning.  With
   // `sort_large`, items with many samples on graphs past the L2s run instead as grouped
   // launches of their own (the plain path's grouping passes and sorted sampling
-  // kernel), beside the persistent kernel, adding into their histogram slots.
+  // kernel), queued beside the persistent kernel, adding into their histogram slots.
   moss_status run(const std::vector<WorkItem>& work, uint32_t n_slots, uint64_t* bins_out, double* device_ms,
                   hipStream_t wait_on, uint32_t tile_samples = 0, uint32_t blocks_per_cu = 0,
                   bool sort_large = false);
 
   int device() const { return device_; }
 
-  // Frees the runner's device buffers, graph and stream (the runner stays usable).
+  // Frees the runner's device buffers and streams (the runner stays usable).
   void release();
 
  private:
@@ -45,7 +45,7 @@ class BatchRunner {
 
   int device_;
   hipStream_t stream_ = nullptr;
-  hipStream_t side_[2] = {};  // the grouped launches in two chains, beside the persistent kernel
+  hipStream_t side_[2] = {};  // the grouped launches in two chains
   hipEvent_t ev_wait_ = nullptr, ev_clear_ = nullptr, ev_side_[2] = {};
   unsigned char* d_in_ = nullptr;          // views, items, control words (kCtl*)
   unsigned char* h_in_ = nullptr;          // their pinned staging

@@ -231,8 +231,8 @@ int edge_filter_bits(int64_t m);
 // 2^19 edges; below, the edge filter itself stays cached).  Measured with rows of at least
 // 4096 / 2048 / 1024 / 512 / 256 / 128 entries (none: 12.68 ms, 442 us): 1e8 samples at
 // n = 1e6, m = 1e7, k = 5, 12.19 / 11.99 / 11.78 / 11.62 / 11.51 / 11.45 ms; 1e7 samples at
-// n = 1e5, m = 1e6, k = 4, 435 / 436 / 431 / 429 / 429 / 430 us.  Building them takes 65 us
-// of the 2.9 ms of all tables at m = 1e7.  A row lists its edges only in a checked CSR (in an
+// n = 1e5, m = 1e6, k = 4, 435 / 436 / 431 / 429 / 429 / 430 us.  Building them takes 53 us
+// of the 2.04 ms of all tables at m = 1e7.  A row lists its edges only in a checked CSR (in an
 // unchecked one the edge set takes every edge from its smaller end), so unchecked graphs do
 // without.
 constexpr int32_t kHubMinDegree = 256;

@@ -913,7 +913,9 @@ bool edge_set_by_buckets(int64_t m, int hash_bits) {
   return m >= kBucketMinEdges && hash_bits >= kBucketBits && hash_bits - kBucketBits <= kMaxBucketBits;
 }
 
-int64_t edge_bucket_count(int hash_bits) { return 1ll << std::max(0, std::min(hash_bits - kBucketBits, kMaxBucketBits)); }
+int64_t edge_bucket_count(int hash_bits) {
+  return 1ll << std::max(0, std::min(hash_bits - kBucketBits, kMaxBucketBits));
+}
 
 uint32_t spill_capacity(int hash_bits) {
   return (uint32_t)std::min<int64_t>(kSpillCap, edge_bucket_count(hash_bits) * kBucketSpill);
@@ -1042,7 +1044,8 @@ __global__ __launch_bounds__(256) void k_span_prefix(RowTables t, uint32_t* err)
     for (int k = 0; k < kPer; ++k) {
       const bool valid = S + lane + 64 * k < t.nnz;
       if (M == kRowSigma) {  // d_x - 1 of the neighbour x
-        const uint2 ends = load_pair(t.rp + (valid ? (int32_t)raw[k] : 0));  // (130 us at m = 1e7; from the node records, four times the bytes, 192)
+        // from the row pointers: 130 us at m = 1e7; from the node records, four times the bytes, 192
+        const uint2 ends = load_pair(t.rp + (valid ? (int32_t)raw[k] : 0));
         x[k] = valid ? (uint64_t)(ends.y - ends.x) - 1 : 0ull;
       } else if (M == kRowTau) {  // (d_x - 1)(S_v - (d_x - 1)), d_x - 1 from the sigma prefix
         const uint64_t p = __shfl(raw[k], (lane + 63) & 63, 64);
@@ -1476,10 +1479,10 @@ __global__ __launch_bounds__(256) void k_rank_mirror(int64_t nnz, const int32_t*
 //                             puts the entry (v, x) at the index of (x, v): the entries
 //                             of column x come in row order, i.e. in the order of row x,
 //                             and symmetry gives column x exactly d_x places from
-//                             row_ptr[x] on.  Two LSD radix passes over the column's bits
-//                             (one block per 8192-entry tile: count, exclusive scan of the
-//                             digit-major counts, stable scatter) carry d_{v,x} along, so
-//                             the second pass writes it straight into rank[mirror].y
+//                             row_ptr[x] on.  Up to three LSD radix passes over the column's bits
+//                             (8 a pass; one block per 8192-entry tile: count, exclusive scan of
+//                             the digit-major counts, stable scatter) carry d_{v,x} along,
+//                             so the last pass writes it straight into rank[mirror].y
 // Within a row, entries of equal degree rank by descending place, which is descending id
 // in a sorted row (the order of Section 3.2's example); repeated neighbours (possible
 // only in an unchecked CSR) get distinct ranks in some order.
@@ -1649,7 +1652,9 @@ __global__ __launch_bounds__(256) void k_rank_short(int64_t nnz, const int32_t* 
       }
 #pragma unroll
       for (int c = 0; c < kPer; ++c)
-        if (own[c]) key[lane + 64 * c] = (uint64_t)((s1[c] - s0[c] + 1u) << 16 | (Ascending ? lane + 64 * c : 0u)) << 32 | xs[c];
+        if (own[c])
+          key[lane + 64 * c] =
+              (uint64_t)((s1[c] - s0[c] + 1u) << 16 | (Ascending ? lane + 64 * c : 0u)) << 32 | xs[c];
     }
     wave_lds_sync();
 #pragma unroll 1
@@ -2079,8 +2084,8 @@ hipError_t launch_rank_tables(const RankTables& t, hipStream_t s) {
   const int zero_mirror = sort_mirror ? 0 : 1;
   hipError_t e = hipSuccess;
   if (fast_local) {
-    hipLaunchKernelGGL(t.validated ? k_rank_short<true> : k_rank_short<false>, dim3(spans_grid(t.nnz)), block, 0, s, t.nnz, t.span_row, t.rec, t.col,
-                       t.acc_sigma, zero_mirror, rank32, t.col_rank);
+    hipLaunchKernelGGL(t.validated ? k_rank_short<true> : k_rank_short<false>, dim3(spans_grid(t.nnz)), block, 0, s,
+                       t.nnz, t.span_row, t.rec, t.col, t.acc_sigma, zero_mirror, rank32, t.col_rank);
     const int passes = t.max_degree < 256 ? 1 : 2;
     if (t.max_degree > kItem) {  // the lists and their counters live in `work` until the mirror sort
       uint32_t* counters = t.work;
@@ -2167,13 +2172,13 @@ int edge_hash_bits(int64_t m) {
 }
 
 // Edge filter: 2^bits 64-bit words, at least 8 bits per edge while that stays within
-// 8 MB, else the larger of 8 MB and 4 bits per edge.  At 8.4 bits per edge about 2% of
-// non-edges get through to the hash set, at 4.2 about 14%.  Measured with the grouped
-// schedule: n = 1e5, m = 1e6 (MOSS-4, 1e7 samples), 0.5 MB of filter (4.2 bits) 0.560
-// ms, 1 MB (8.4 bits) 0.514 ms; n = 1e6, m = 1e7 (T-5 / Path-5, 5e7 samples each), 8 MB
-// (6.7 bits) 5.61 / 8.06 ms, 16 MB (13.4 bits) 6.09 / 8.39 ms, 4 MB (3.4 bits) 5.85 /
-// 8.31 ms.  Past a few MB the filter no longer stays in the L2s and its own misses
-// cost more than the hash-set reads it saves.
+// 8 MB, else the larger of 8 MB and 4 bits per edge.  At 16.8 bits per edge 0.5% of
+// non-edges get through to the hash set, at 8.4 3.0%, at 6.7 5.4%, at 4.2 16%.  An estimate
+// with 0.5 / 1 / 2 MB of filter (4.2 / 8.4 / 16.8 bits), hub filters beside it: n = 1e5,
+// m = 1e6, MOSS-4 for 1e7 samples, 415 / 401 / 414 us; with 4 / 8 / 16 MB (3.4 / 6.7 / 13.4
+// bits): n = 1e6, m = 1e7, 1e8 5-node samples, 11.80 / 11.38 / 11.50 ms.  Past a few MB the
+// filter no longer stays in the L2s and its own misses cost more than the hash-set reads
+// it saves.
 constexpr double kFilterBitsPerEdge = 8.0;
 constexpr double kFilterMinBitsPerEdge = 4.0;
 constexpr int kFilterCapBits = 20;  // 2^20 words = 8 MB
@@ -2803,9 +2808,11 @@ __device__ __forceinline__ void flush_hits(const uint32_t (&bins)[kMaxWaves][kBi
     if (lane == kHostTicks)
       sum = wall_clock64() - atomicExch(&all[kHitStart], 0ull);
     static_assert(kHostTicks == 2 * kBins, "the ticks follow the counts");
-    if (lane <= kHostTicks) __hip_atomic_store(&k.host[lane], (unsigned long long)sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (lane <= kHostTicks)
+      __hip_atomic_store(&k.host[lane], (unsigned long long)sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __threadfence_system();
-    if (lane == 0) __hip_atomic_store(&k.host[kHostSeq], (unsigned long long)k.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (lane == 0)
+      __hip_atomic_store(&k.host[kHostSeq], (unsigned long long)k.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -2907,7 +2914,8 @@ __device__ __forceinline__ void draw_chunks(const SamplerView& a, uint64_t seed,
 // blocks[0] blocks draw the first sampler's samples, the others the second's, so that two
 // samplers of a small estimate, neither of which fills the chip, run side by side.
 template <int S0, int S1>
-__global__ __launch_bounds__(256, kSampleWaves) void k_sample(PlainJob p, HitSink sink, uint8_t* __restrict__ class_out) {
+__global__ __launch_bounds__(256, kSampleWaves) void k_sample(PlainJob p, HitSink sink,
+                                                              uint8_t* __restrict__ class_out) {
   __shared__ uint32_t bins[kMaxWaves][kBins + 2];
   __shared__ uint8_t lut[64];
   __shared__ LaneSort<kLaneChunk> ls;
@@ -3313,9 +3321,9 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(SortJobs jobs) {
 }
 
 template <int S>
-__global__ __launch_bounds__(256, kSampleWaves) void k_sample_sorted(SamplerView a, uint64_t seed, uint64_t k0, uint64_t n,
-                                                       SortScratch t, uint32_t window, HitSink sink,
-                                                       uint8_t* __restrict__ class_out) {
+__global__ __launch_bounds__(256, kSampleWaves) void k_sample_sorted(SamplerView a, uint64_t seed, uint64_t k0,
+                                                                     uint64_t n, SortScratch t, uint32_t window,
+                                                                     HitSink sink, uint8_t* __restrict__ class_out) {
   __shared__ uint32_t bins[kMaxWaves][kBins + 2];
   __shared__ uint8_t lut[64];
   __shared__ uint32_t s_win;
@@ -3550,7 +3558,8 @@ hipError_t launch_batch_stage(const void* host, void* dev, size_t bytes, unsigne
   const uint64_t quads = bytes / 16;
   if (bytes % 16) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_batch_stage, dim3((unsigned)std::max(1, std::min(fill_grid(std::max(quads, words)), 256))),
-                     dim3(256), 0, s, static_cast<const uint4*>(host), static_cast<uint4*>(dev), quads, bins, words, end);
+                     dim3(256), 0, s, static_cast<const uint4*>(host), static_cast<uint4*>(dev), quads, bins, words,
+                     end);
   return hipGetLastError();
 }
 
